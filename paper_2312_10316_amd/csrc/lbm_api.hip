@@ -219,6 +219,37 @@ Launch fused_default(const lbm_params &p, int mode)
     return lc;
 }
 
+// Rows of a strip of T steps on an nx x ny lattice.  A strip of H rows computes T H + T (T - 1) node rows
+// (each step's rows beyond the strip's are recomputed by its neighbours), so tall strips waste less
+// and short ones fill the chip.  Time of a launch in units of one node row at full issue rate: 12 for
+// the launch, and per generation of resident waves (`occ` per SIMD) alone[w] per node row with w waves
+// on a SIMD, from runs at 64^2 .. 2048^2 (FP32 0.28 / 0.41 / 0.57 us, FP64 0.32 / 0.57 us per node row
+// with 1 / 2 / 3 waves): 1024^2 FP32 12 rows 157k MLUPS, 16 rows 131k, 4 rows 147k; 2048^2 38 rows
+// 215k, 16 rows 196k, 50 rows 181k.  From eight generations of 16-row strips on, the count no
+// longer matters and short strips keep the columns that neighbouring strips share in L2: FP32 16 rows
+// (4096^2 216k, 32 rows 203k), FP64 24 rows (8192^2 125.6k, 16 rows 123.2k).
+int strip_rows(int mode, int nx, int ny)
+{
+    const bool f64 = mode == MODE_F64_F64;
+    const double alone[4] = {0.0, f64 ? 1.92 : 1.67, f64 ? 3.42 : 2.46, 3.4};
+    const int occ = f64 ? 2 : 3, T = kStripSteps;
+    const int64_t ns = (nx + strip_width(T) - 1) / strip_width(T);
+    const auto per_simd = [&](int h) { return (double)(ns * ((ny + h - 1) / h)) / 1024.0; };
+    if (per_simd(16) >= 8.0) return f64 ? 24 : 16;
+    int best = 2;
+    double least = 0.0;
+    for (int h = 2; h <= 40; ++h) {
+        const int w = (int)std::ceil(per_simd(h));
+        const double gens = (w / occ) * alone[occ] + alone[w % occ];
+        const double t = 12.0 + gens * (T * h + T * (T - 1)) * (1.0 + 2.0 / (h + 8));
+        if (h == 2 || t < least) {
+            best = h;
+            least = t;
+        }
+    }
+    return best;
+}
+
 // One buffer updated in place (AA pattern): a context of one periodic instance, D2Q9 with the local or
 // no aux term, or D3Q19/D3Q27 except FP64 math (whose one-row in-place kernels fuse the collision's
 // multiply-adds otherwise than the two-buffer walking loop: equal to rounding, not bitwise).
@@ -393,10 +424,10 @@ InstDesc desc_of(const Instance &in)
 
 }  // namespace
 
-// Long runs replay a captured graph of kGraphSteps steps (an even count, so every buffer returns
-// to its role); one graph per buffer parity, dropped whenever a descriptor or the schedule changes.
+// Long runs replay a captured graph of kGraphSteps steps (an even number of launches, so every buffer
+// returns to its role); one graph per buffer parity, dropped whenever a descriptor or the schedule changes.
 constexpr int kGraphSteps = 32;
-static_assert(kGraphSteps % 2 == 0, "a graph replay must keep the buffer parity");
+static_assert(kGraphSteps % 4 == 0 && kGraphSteps % (2 * kStripSteps) == 0, "a graph replay must keep the buffer parity");
 
 // Device scratch of lbm_macros_static: the per-block partial sums of the diagnostics reduction
 // (kMacroBlocks x kMacroPartialDoubles) and its final result (8 doubles).  One copy per GPU, held until
@@ -419,10 +450,19 @@ struct Schedule {
     std::vector<int32_t> h_block_start;
 };
 
+// Launch of the strip kernel: rows per strip (0: the instance does not use it) and the store kind.
+struct StripLaunch {
+    int rows = 0;
+    bool cached = false;
+};
+
 struct lbm_ctx {
     std::vector<Instance> inst;
     int parity = 0;                   // the buffer every instance currently reads (they step together)
     bool uniform = false;             // all instances share mode and aux (a batched launch is possible)
+    StripLaunch strips;               // several steps per launch on strips (rows 0: never)
+    lbm_launch strips_with = {};      // the launch shape the strips belong to (the default one)
+    bool strips_on = false;           // the launch shape is that one
     bool l2_streams = false;          // steps stream their stores although the state fits the caches
     lbm_batch batch = {LBM_BATCH_SERIAL, 0, 0};
     InstDesc *d_desc = nullptr;       // device tables (in the workspace)
@@ -557,6 +597,22 @@ int refresh_tables(lbm_ctx *c)
     return e == hipSuccess ? LBM_OK : hip_fail(e, "synchronizing after a table update");
 }
 
+// The strip launch of a context's one instance in its default launch shape, or rows 0: a periodic D2Q9
+// TRT-R instance with the local or no aux term and FP64 or FP32 storage in two buffers, of at least 16
+// rows (a shorter lattice would recompute more than it saves).  `touched`: bytes its steps touch.
+// Stores: the default launch's kind (cached within the Infinity Cache); FP32 states of more than twice
+// that cache are stored cached too, which merges the lines that neighbouring strips share (8192^2 211k
+// -> 221k, 4096^2 206k -> 216k MLUPS; 2048^2, 1.3 times the cache, 215k streaming, 203k cached), FP64
+// ones stream (8192^2 125.6k, cached 110.8k).
+StripLaunch strip_default(const Instance &in, size_t touched)
+{
+    StripLaunch s;
+    if (!fusable(in.p) || in.p.aux == LBM_AUX_FLUX || is_f16_mode(in.mode) || in.p.ny < 16 || in.lc.stores == 2) return s;
+    s.rows = strip_rows(in.mode, in.p.nx, in.p.ny);
+    s.cached = in.lc.stores == 1 || (in.mode == MODE_F32_F32 && touched > 2 * kInfinityCacheBytes);
+    return s;
+}
+
 int prep_field(lbm_ctx *c, Instance &in, const double *a, const double *b, double ca, double cb, void *out,
                int check_positive, int stride = 1, int comp = 0)
 {
@@ -652,6 +708,18 @@ int enqueue_fused(lbm_ctx *c, hipStream_t st)
     return LBM_OK;
 }
 
+// Enqueues kStripSteps steps of a context's one instance.
+int enqueue_strips(lbm_ctx *c, hipStream_t st)
+{
+    StepArgs a;
+    a.d = c->h_desc[0];
+    a.parity = c->parity;
+    hipError_t e = launch_strips(c->inst[0].mode, c->inst[0].p.aux, a, c->strips.rows, c->strips.cached, st);
+    if (e != hipSuccess) return hip_fail(e, "strip kernel launch");
+    c->parity ^= 1;
+    return LBM_OK;
+}
+
 // Returns the graph of kGraphSteps steps for the current buffer parity, capturing it if needed.
 int graph_for(lbm_ctx *c, hipGraphExec_t *out)
 {
@@ -667,7 +735,9 @@ int graph_for(lbm_ctx *c, hipGraphExec_t *out)
     hipError_t e = hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     int rc = LBM_OK;
-    if (fused(c))
+    if (c->strips_on)
+        for (int t = 0; t < kGraphSteps / kStripSteps && rc == LBM_OK; ++t) rc = enqueue_strips(c, c->capture);
+    else if (fused(c))
         for (int t = 0; t < kGraphSteps / 2 && rc == LBM_OK; ++t) rc = enqueue_fused(c, c->capture);
     else
         for (int t = 0; t < kGraphSteps && rc == LBM_OK; ++t) rc = enqueue_step(c, c->capture);
@@ -873,6 +943,11 @@ int lbm_init(lbm_ctx **out, int32_t n_inst, const lbm_params *p, const lbm_field
         }
         if (inplace) in.buf[1] = in.buf[0];
     }
+    if (n_inst == 1) {
+        c->strips = strip_default(i0, touched);
+        c->strips_on = c->strips.rows > 0;
+        lbm_get_launch(c, 0, &c->strips_with);
+    }
     const size_t items = max_items_of(n_inst, p);
     c->d_desc = reinterpret_cast<InstDesc *>(w);
     w += align_up((size_t)n_inst * sizeof(InstDesc), kAlign);
@@ -977,6 +1052,11 @@ int lbm_step(lbm_ctx *c, int32_t nsteps, const double *const *ux, const double *
             if (e != hipSuccess) return account(hip_fail(e, "hipGraphLaunch"));
         }
     }
+    if (c->strips_on)
+        for (; left >= kStripSteps; left -= kStripSteps) {
+            rc = enqueue_strips(c, c->stream);
+            if (rc) return account(rc);
+        }
     if (fused(c))
         for (; left >= 2; left -= 2) {
             rc = enqueue_fused(c, c->stream);
@@ -1210,6 +1290,11 @@ int lbm_set_launch(lbm_ctx *c, int32_t inst, const lbm_launch *cfg)
         else in.lc1.stores = lc.stores;
     }
     c->l2_streams = false;  // the caller's store kind holds for the adjoint's recomputation too
+    if (c->strips.rows > 0) {  // strips go with the default launch shape, and again with it
+        lbm_launch now = {};
+        lbm_get_launch(c, 0, &now);
+        c->strips_on = std::memcmp(&now, &c->strips_with, sizeof now) == 0;
+    }
     return refresh_tables(c);
 }
 

@@ -199,6 +199,11 @@ hipError_t launch_step(int mode, int aux, const StepArgs &a, hipStream_t st);
 // Two steps per launch (lbm_fused.hip): D2Q9, periodic, aux LOCAL or NONE, two buffers (reads
 // buf[parity], writes buf[parity ^ 1] two steps later).  lcf.fuse_width columns x lcf.rows rows per tile.
 hipError_t launch_step2(int mode, int aux, const StepArgs &a, hipStream_t st);
+// kStripSteps steps per launch on strips of `rows` rows that one wave owns (lbm_strips.h): periodic D2Q9
+// TRT-R, aux LOCAL or NONE, FP64 or FP32 storage, two buffers.  cached: as Launch::stores 1, else 0.
+constexpr int kStripSteps = 4;
+constexpr int strip_width(int T) { return 64 - 2 * T; }  // output columns of a strip: a step takes one lane off either end of a wave
+hipError_t launch_strips(int mode, int aux, const StepArgs &a, int rows, bool cached, hipStream_t st);
 // The same for many instances in one launch: block b runs work items (instance, fused tile) as the
 // one-step batched kernel does; every instance has tiles of `width` columns (128, 256 or 512).
 hipError_t launch_batched_step2(int mode, int aux, const BatchArgs &a, int nblocks, int width, hipStream_t st);
