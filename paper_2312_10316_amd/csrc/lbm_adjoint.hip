@@ -13,6 +13,7 @@
 // is computed as R^T C^T H^T mu without forming M.  All in lattice units, like the forward kernel.
 #include "lbm_internal.h"
 #include "lbm_kernel_common.h"
+#include "lbm_strips.h"
 
 namespace lbm {
 namespace {

@@ -233,7 +233,7 @@ int strip_rows(int mode, int nx, int ny)
     const bool f64 = mode == MODE_F64_F64;
     const double alone[4] = {0.0, f64 ? 1.92 : 1.67, f64 ? 3.42 : 2.46, 3.4};
     const int occ = f64 ? 2 : 3, T = kStripSteps;
-    const int64_t ns = (nx + strip_width(T) - 1) / strip_width(T);
+    const int64_t ns = (nx + strip_width(T, 1) - 1) / strip_width(T, 1);
     const auto per_simd = [&](int h) { return (double)(ns * ((ny + h - 1) / h)) / 1024.0; };
     if (per_simd(16) >= 8.0) return f64 ? 24 : 16;
     int best = 2;
@@ -450,12 +450,6 @@ struct Schedule {
     std::vector<int32_t> h_block_start;
 };
 
-// Launch of the strip kernel: rows per strip (0: the instance does not use it) and the store kind.
-struct StripLaunch {
-    int rows = 0;
-    bool cached = false;
-};
-
 struct lbm_ctx {
     std::vector<Instance> inst;
     int parity = 0;                   // the buffer every instance currently reads (they step together)
@@ -598,18 +592,26 @@ int refresh_tables(lbm_ctx *c)
 }
 
 // The strip launch of a context's one instance in its default launch shape, or rows 0: a periodic D2Q9
-// TRT-R instance with the local or no aux term and FP64 or FP32 storage in two buffers, of at least 16
-// rows (a shorter lattice would recompute more than it saves).  `touched`: bytes its steps touch.
-// Stores: the default launch's kind (cached within the Infinity Cache); FP32 states of more than twice
-// that cache are stored cached too, which merges the lines that neighbouring strips share (8192^2 211k
-// -> 221k, 4096^2 206k -> 216k MLUPS; 2048^2, 1.3 times the cache, 215k streaming, 203k cached), FP64
-// ones stream (8192^2 125.6k, cached 110.8k).
+// TRT-R instance with the local or no aux term in two buffers, of at least 16 rows (a shorter lattice
+// would recompute more than it saves).  `touched`: bytes its steps touch.
+// Columns per lane: two for FP16 from 12e6 nodes on (even nx), 48 rows (8192^2 with D 210k MLUPS, one
+// column 196k, two steps per launch 180k; 4096^2 194k, 171k, 166k); one below, except where the state
+// of a narrow lattice stays in the Infinity Cache and 512-column two-step tiles are as fast (2048^2 203k
+// both) or, with stochastic rounding, faster (2048^2 160k against 134k, 1024^2 level).
+// Stores: the default launch's kind (cached within the Infinity Cache); FP32 and FP16 states of more
+// than twice that cache are stored cached too, which merges the lines that neighbouring strips share
+// (FP32 8192^2 208k -> 220k, 4096^2 206k -> 216k MLUPS, FP16 8192^2 218k -> 223k; FP32 2048^2, 1.3 times
+// the cache, 215k streaming, 203k cached), FP64 ones stream (8192^2 125.6k, cached 110.8k).
 StripLaunch strip_default(const Instance &in, size_t touched)
 {
     StripLaunch s;
-    if (!fusable(in.p) || in.p.aux == LBM_AUX_FLUX || is_f16_mode(in.mode) || in.p.ny < 16 || in.lc.stores == 2) return s;
-    s.rows = strip_rows(in.mode, in.p.nx, in.p.ny);
-    s.cached = in.lc.stores == 1 || (in.mode == MODE_F32_F32 && touched > 2 * kInfinityCacheBytes);
+    const int64_t nodes = (int64_t)in.p.nx * in.p.ny;
+    const bool f16 = is_f16_mode(in.mode), pairs = f16 && in.p.nx % 2 == 0 && nodes >= 12000000;
+    if (!fusable(in.p) || in.p.aux == LBM_AUX_FLUX || in.p.ny < 16 || in.lc.stores == 2) return s;
+    if (f16 && !pairs && (in.mode == MODE_F16SR_F32 || (in.p.nx <= 2048 && nodes >= fuse_min_nodes(in.mode)))) return s;
+    s.rows = pairs ? 48 : strip_rows(in.mode, in.p.nx, in.p.ny);
+    s.cols = pairs ? 2 : 1;
+    s.cached = in.lc.stores == 1 || (store_bytes(in.mode) < 8 && touched > 2 * kInfinityCacheBytes);
     return s;
 }
 
@@ -714,7 +716,7 @@ int enqueue_strips(lbm_ctx *c, hipStream_t st)
     StepArgs a;
     a.d = c->h_desc[0];
     a.parity = c->parity;
-    hipError_t e = launch_strips(c->inst[0].mode, c->inst[0].p.aux, a, c->strips.rows, c->strips.cached, st);
+    hipError_t e = launch_strips(c->inst[0].mode, c->inst[0].p.aux, a, c->strips, st);
     if (e != hipSuccess) return hip_fail(e, "strip kernel launch");
     c->parity ^= 1;
     return LBM_OK;

@@ -23,7 +23,6 @@
 // per row suffices.
 #include "lbm_internal.h"
 #include "lbm_kernel_common.h"
-#include "lbm_strips.h"
 
 namespace lbm {
 namespace {
@@ -866,46 +865,6 @@ hipError_t launch_step2(int mode, int aux, const StepArgs &a, hipStream_t st)
     case MODE_F32_F32: return launch_fused_mode<MODE_F32_F32>(aux, a, st);
     case MODE_F16S_F32: return launch_fused_mode<MODE_F16S_F32>(aux, a, st);
     case MODE_F16SR_F32: return launch_fused_mode<MODE_F16SR_F32>(aux, a, st);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-namespace {
-
-template <int MODE, int AUX, bool CST>
-hipError_t launch_strips_st(const StepArgs &a, int rows, hipStream_t st)
-{
-    const int64_t ns = (a.d.L.nx + strip_width(kStripSteps) - 1) / strip_width(kStripSteps);
-    const int64_t nb = (ns * ((a.d.L.ny + rows - 1) / rows) + 3) / 4;
-    if (nb > INT32_MAX / 4) return hipErrorInvalidValue;
-    const bool hk = a.d.has_k, hs = a.d.has_s;
-    if (hk && hs) strip_kernel<MODE, AUX, true, true, kStripSteps, CST><<<(int)nb, 256, 0, st>>>(a, rows);
-    else if (hk) strip_kernel<MODE, AUX, true, false, kStripSteps, CST><<<(int)nb, 256, 0, st>>>(a, rows);
-    else if (hs) strip_kernel<MODE, AUX, false, true, kStripSteps, CST><<<(int)nb, 256, 0, st>>>(a, rows);
-    else strip_kernel<MODE, AUX, false, false, kStripSteps, CST><<<(int)nb, 256, 0, st>>>(a, rows);
-    return hipGetLastError();
-}
-
-template <int MODE>
-hipError_t launch_strips_mode(int aux, const StepArgs &a, int rows, bool cached, hipStream_t st)
-{
-    switch (aux) {
-    case 0: return cached ? launch_strips_st<MODE, 0, true>(a, rows, st) : launch_strips_st<MODE, 0, false>(a, rows, st);
-    case 2: return cached ? launch_strips_st<MODE, 2, true>(a, rows, st) : launch_strips_st<MODE, 2, false>(a, rows, st);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-}  // namespace
-
-hipError_t launch_strips(int mode, int aux, const StepArgs &a, int rows, bool cached, hipStream_t st)
-{
-    if (a.d.L.q != 9 || a.d.bckind != 0 || a.d.w3 != 0.0 || rows < 1 || a.d.buf[0] == a.d.buf[1])
-        return hipErrorInvalidValue;
-    switch (mode) {
-    case MODE_F64_F64: return launch_strips_mode<MODE_F64_F64>(aux, a, rows, cached, st);
-    case MODE_F64_F32: return launch_strips_mode<MODE_F64_F32>(aux, a, rows, cached, st);
-    case MODE_F32_F32: return launch_strips_mode<MODE_F32_F32>(aux, a, rows, cached, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -199,11 +199,17 @@ hipError_t launch_step(int mode, int aux, const StepArgs &a, hipStream_t st);
 // Two steps per launch (lbm_fused.hip): D2Q9, periodic, aux LOCAL or NONE, two buffers (reads
 // buf[parity], writes buf[parity ^ 1] two steps later).  lcf.fuse_width columns x lcf.rows rows per tile.
 hipError_t launch_step2(int mode, int aux, const StepArgs &a, hipStream_t st);
-// kStripSteps steps per launch on strips of `rows` rows that one wave owns (lbm_strips.h): periodic D2Q9
-// TRT-R, aux LOCAL or NONE, FP64 or FP32 storage, two buffers.  cached: as Launch::stores 1, else 0.
+// kStripSteps steps per launch on strips of `rows` rows and `cols` columns per lane that one wave owns
+// (lbm_strips.h): periodic D2Q9 TRT-R, aux LOCAL or NONE, two buffers; cols 2 for FP16 storage and even nx.
 constexpr int kStripSteps = 4;
-constexpr int strip_width(int T) { return 64 - 2 * T; }  // output columns of a strip: a step takes one lane off either end of a wave
-hipError_t launch_strips(int mode, int aux, const StepArgs &a, int rows, bool cached, hipStream_t st);
+// Output columns of a strip of NC columns per lane: each step takes one column off either end of a wave.
+constexpr int strip_width(int T, int NC) { return 64 * NC - 2 * T; }
+struct StripLaunch {
+    int rows = 0;         // 0: the instance does not run on strips
+    int cols = 1;
+    bool cached = false;  // stores: as Launch::stores 1, else 0
+};
+hipError_t launch_strips(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
 // The same for many instances in one launch: block b runs work items (instance, fused tile) as the
 // one-step batched kernel does; every instance has tiles of `width` columns (128, 256 or 512).
 hipError_t launch_batched_step2(int mode, int aux, const BatchArgs &a, int nblocks, int width, hipStream_t st);

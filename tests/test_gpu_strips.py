@@ -63,3 +63,15 @@ def test_another_launch_shape_and_back():
         one.step(18)
         same(one, two)
     assert two.get_launch() == d
+
+
+@pytest.mark.parametrize("mode", ["f16s", "f16sr"])
+@pytest.mark.parametrize("nx,ny,var", [(118, 101700, False), (242, 49600, True), (3466, 3464, True)])
+def test_two_columns_per_lane(mode, nx, ny, var):
+    """FP16 from 12e6 nodes on an even nx: strips of 120 columns (a lattice narrower than one, two columns past
+    two of them, and the smallest square one), rows around 48."""
+    one, two = contexts(mode, nx, ny, lbm.LBM_AUX_LOCAL, var)
+    for n in (4, 7):
+        one.step(n)
+        two.step(n)
+        assert torch.equal(one.state_save(), two.state_save())
