@@ -220,29 +220,31 @@ Launch fused_default(const lbm_params &p, int mode)
 }
 
 // Rows of a strip of T steps on an nx x ny lattice.  A strip of H rows computes T H + T (T - 1) node rows
-// (each step's rows beyond the strip's are recomputed by its neighbours), so tall strips waste less
-// and short ones fill the chip.  Time of a launch in units of one node row at full issue rate: 12 for
-// the launch, and per generation of resident waves (`occ` per SIMD) alone[w] per node row with w waves
-// on a SIMD, from runs at 64^2 .. 2048^2 (FP32 0.28 / 0.41 / 0.57 us, FP64 0.32 / 0.57 us per node row
-// with 1 / 2 / 3 waves): 1024^2 FP32 12 rows 157k MLUPS, 16 rows 131k, 4 rows 147k; 2048^2 38 rows
-// 215k, 16 rows 196k, 50 rows 181k.  From eight generations of 16-row strips on, the count no
-// longer matters and short strips keep the columns that neighbouring strips share in L2: FP32 16 rows
-// (4096^2 216k, 32 rows 203k), FP64 24 rows (8192^2 125.6k, 16 rows 123.2k).
-int strip_rows(int mode, int nx, int ny)
+// (T H + 2 T (T - 1) in the flux form; each step's rows beyond the strip's are recomputed by its
+// neighbours), so tall strips waste less and short ones fill the chip.  Time of a launch in units of one
+// node row at full issue rate: 12 for the launch, and per generation of resident waves (`occ` per SIMD)
+// alone[w] per node row with w waves on a SIMD, from runs at 64^2 .. 2048^2 (FP32 0.32 / 0.41 / 0.57 us, FP64
+// 0.32 / 0.57 us per node row with 1 / 2 / 3 waves), times a term for the rows that two strips read:
+// 1024^2 FP32 10 rows 169k MLUPS, 12 rows 154k, 4 rows 140k; 2048^2 38 rows 206k, 26 rows 200k, 16 rows 191k.
+// From eight generations of 16-row strips on the count no longer matters: 24 rows (with two waves per SIMD
+// FP32 8192^2 223k MLUPS, 16 rows 212k; FP64 125.6k, 123.2k), in the flux form 64 (FP32 8192^2 198k, 32
+// rows 186k; FP64 4096^2 82.8k, 24 rows 74.5k; FP16 8192^2 157k, 144k).
+int strip_rows(int mode, int nx, int ny, bool flux)
 {
     const bool f64 = mode == MODE_F64_F64;
-    const double alone[4] = {0.0, f64 ? 1.92 : 1.67, f64 ? 3.42 : 2.46, 3.4};
-    const int occ = f64 ? 2 : 3, T = kStripSteps;
-    const int64_t ns = (nx + strip_width(T, 1) - 1) / strip_width(T, 1);
+    const double alone[4] = {0.0, f64 ? 1.92 : 1.9, f64 ? 3.42 : 2.46, 3.4};
+    const int occ = f64 ? 2 : 3, T = flux ? kFluxStripSteps : kStripSteps;
+    const int V = strip_width(flux ? 2 * T : T, 1), extra = (flux ? 2 : 1) * T * (T - 1);
+    const int64_t ns = (nx + V - 1) / V;
     const auto per_simd = [&](int h) { return (double)(ns * ((ny + h - 1) / h)) / 1024.0; };
-    if (per_simd(16) >= 8.0) return f64 ? 24 : 16;
-    int best = 2;
+    if (per_simd(16) >= 8.0) return flux ? 64 : 24;
+    int best = 1;
     double least = 0.0;
-    for (int h = 2; h <= 40; ++h) {
-        const int w = (int)std::ceil(per_simd(h));
+    for (int h = 1; h <= 40; ++h) {
+        const int w = (int)std::ceil(1.02 * per_simd(h));  // a count just under a whole one spills over on some CUs
         const double gens = (w / occ) * alone[occ] + alone[w % occ];
-        const double t = 12.0 + gens * (T * h + T * (T - 1)) * (1.0 + 2.0 / (h + 8));
-        if (h == 2 || t < least) {
+        const double t = 12.0 + gens * (T * h + extra) * (1.0 + 4.0 / (h + 8));
+        if (h == 1 || t < least) {
             best = h;
             least = t;
         }
@@ -372,6 +374,20 @@ size_t max_items2_of(int32_t n_inst, const lbm_params *p)
     return items;
 }
 
+// Strips of kBatchStripRows rows (four steps per launch).
+constexpr int kBatchStripRows = 16;
+int64_t batch_strips_of(const lbm_params &p)
+{
+    constexpr int V = strip_width(kStripSteps, 1);
+    return (int64_t)((p.nx + V - 1) / V) * ((p.ny + kBatchStripRows - 1) / kBatchStripRows);
+}
+size_t max_items3_of(int32_t n_inst, const lbm_params *p)
+{
+    size_t items = 0;
+    for (int k = 0; k < n_inst; ++k) items += (size_t)batch_strips_of(p[k]);
+    return items;
+}
+
 // Shared scratch: macro partials, the macro result, two flag words; then the batch tables
 // (instance descriptors, work items, block ranges).
 constexpr size_t kPartialBytes = (size_t)kMacroBlocks * kMacroPartialDoubles * sizeof(double);
@@ -380,7 +396,8 @@ constexpr size_t kScratchBytes = kPartialBytes + 256 + 256;
 size_t tables_bytes(int32_t n_inst, const lbm_params *p)
 {
     size_t b = align_up((size_t)n_inst * sizeof(InstDesc), kAlign) + align_up((size_t)n_inst * 2 * sizeof(int64_t), kAlign);
-    for (size_t items : {max_items_of(n_inst, p), n_inst > 1 ? max_items2_of(n_inst, p) : (size_t)0})
+    for (size_t items : {max_items_of(n_inst, p), n_inst > 1 ? max_items2_of(n_inst, p) : (size_t)0,
+                         n_inst > 1 ? max_items3_of(n_inst, p) : (size_t)0})
         b += align_up(items * sizeof(WorkItem), kAlign) + align_up((items + 1) * sizeof(int32_t), kAlign);
     return b;
 }
@@ -427,7 +444,8 @@ InstDesc desc_of(const Instance &in)
 // Long runs replay a captured graph of kGraphSteps steps (an even number of launches, so every buffer
 // returns to its role); one graph per buffer parity, dropped whenever a descriptor or the schedule changes.
 constexpr int kGraphSteps = 32;
-static_assert(kGraphSteps % 4 == 0 && kGraphSteps % (2 * kStripSteps) == 0, "a graph replay must keep the buffer parity");
+static_assert(kGraphSteps % 4 == 0 && kGraphSteps % (2 * kStripSteps) == 0 && kGraphSteps % (2 * kFluxStripSteps) == 0,
+              "a graph replay must keep the buffer parity");
 
 // Device scratch of lbm_macros_static: the per-block partial sums of the diagnostics reduction
 // (kMacroBlocks x kMacroPartialDoubles) and its final result (8 doubles).  One copy per GPU, held until
@@ -456,12 +474,13 @@ struct lbm_ctx {
     bool uniform = false;             // all instances share mode and aux (a batched launch is possible)
     StripLaunch strips;               // several steps per launch on strips (rows 0: never)
     lbm_launch strips_with = {};      // the launch shape the strips belong to (the default one)
-    bool strips_on = false;           // the launch shape is that one
+    lbm_batch strips_batch = {};      // and the batch schedule
+    bool strips_on = false;           // every instance has that shape, and the context that schedule
     bool l2_streams = false;          // steps stream their stores although the state fits the caches
     lbm_batch batch = {LBM_BATCH_SERIAL, 0, 0};
     InstDesc *d_desc = nullptr;       // device tables (in the workspace)
     std::vector<InstDesc> h_desc;     // host staging of the descriptors
-    Schedule sched[2];                // batched work lists: one step per launch, two steps per launch
+    Schedule sched[3];                // batched work lists: one, two, kStripSteps steps per launch
     hipStream_t stream = nullptr;
     hipStream_t capture = nullptr;    // private stream used only to record graphs
     int lds_per_cu = 0;               // LDS bytes per CU of the device (for the wave cap)
@@ -570,6 +589,30 @@ int build_schedule(lbm_ctx *c, bool two)
     return e == hipSuccess ? LBM_OK : hip_fail(e, "uploading work items");
 }
 
+// The work list of the batched strip launch: every strip of every instance, in instance order.
+int build_strip_schedule(lbm_ctx *c)
+{
+    Schedule &sc = c->sched[2];
+    sc.h_items.clear();
+    for (int k = 0; k < (int)c->inst.size(); ++k)
+        for (int64_t t = 0; t < batch_strips_of(c->inst[k].p); ++t) sc.h_items.push_back(WorkItem{k, (int32_t)t});
+    sc.nblocks = (int)sc.h_items.size();
+    hipError_t e = hipMemcpyAsync(sc.d_items, sc.h_items.data(), sc.h_items.size() * sizeof(WorkItem), hipMemcpyHostToDevice,
+                                  c->stream);
+    return e == hipSuccess ? LBM_OK : hip_fail(e, "uploading strip work items");
+}
+
+// Strips go with the default launch shape and batch schedule, and again when the caller sets those.
+void update_strips(lbm_ctx *c)
+{
+    c->strips_on = c->strips.rows > 0 && std::memcmp(&c->batch, &c->strips_batch, sizeof c->batch) == 0;
+    for (int k = 0; k < (int)c->inst.size() && c->strips_on; ++k) {
+        lbm_launch now = {};
+        lbm_get_launch(c, k, &now);
+        c->strips_on = std::memcmp(&now, &c->strips_with, sizeof now) == 0;
+    }
+}
+
 // Rebuilds the descriptors and (for a batched policy) the work list, and uploads them.  The host
 // staging vectors are only rewritten after the stream has drained.
 int refresh_tables(lbm_ctx *c)
@@ -585,33 +628,57 @@ int refresh_tables(lbm_ctx *c)
     if (batched(c)) {
         int rc = build_schedule(c, false);
         if (rc == LBM_OK && fused(c)) rc = build_schedule(c, true);
+        if (rc == LBM_OK && c->strips.rows > 0) rc = build_strip_schedule(c);
         if (rc) return rc;
     }
     e = hipStreamSynchronize(c->stream);
     return e == hipSuccess ? LBM_OK : hip_fail(e, "synchronizing after a table update");
 }
 
-// The strip launch of a context's one instance in its default launch shape, or rows 0: a periodic D2Q9
-// TRT-R instance with the local or no aux term in two buffers, of at least 16 rows (a shorter lattice
-// would recompute more than it saves).  `touched`: bytes its steps touch.
-// Columns per lane: two for FP16 from 12e6 nodes on (even nx), 48 rows (8192^2 with D 210k MLUPS, one
-// column 196k, two steps per launch 180k; 4096^2 194k, 171k, 166k); one below, except where the state
-// of a narrow lattice stays in the Infinity Cache and 512-column two-step tiles are as fast (2048^2 203k
-// both) or, with stochastic rounding, faster (2048^2 160k against 134k, 1024^2 level).
+// The strip launch of a context in its default launch shape, or rows 0.  `touched`: bytes its steps touch.
+// One D2Q9 TRT-R instance in two buffers, periodic or between walls, of at least 16 rows (a shorter lattice
+// would recompute more than it saves), or a uniform batch of such (periodic, FP64 or FP32 storage).
+// Measured in MLUPS, without strips / with: local aux term FP32 2048^2 131k / 206k, 8192^2 140k / 223k,
+// 256^2 24k / 31k, FP64 8192^2 69k / 126k; flux form FP32 2048^2 92k / 164k, 512^2 32k / 47k, FP64 4096^2
+// 57k / 83k; walls FP32 1000 x 500 63k / 104k, FP64 300 x 100 6k / 11k; 128 instances of 32^2 .. 512^2 FP32
+// 105k / 178k.
+// Columns per lane: two for FP16 from 12e6 nodes on (even nx, local or no aux term), 48 rows (8192^2 with D
+// 180k / 210k, one column 196k; 4096^2 166k / 194k, one column 171k).  FP16 states of narrow lattices that
+// fill 512-column tiles stay on two-step tiles (2048^2 203k, strips 190k; flux form 132k, 124k), as do those
+// with stochastic rounding below 12e6 nodes (2048^2 160k, strips 134k; 1024^2 level).
 // Stores: the default launch's kind (cached within the Infinity Cache); FP32 and FP16 states of more
 // than twice that cache are stored cached too, which merges the lines that neighbouring strips share
-// (FP32 8192^2 208k -> 220k, 4096^2 206k -> 216k MLUPS, FP16 8192^2 218k -> 223k; FP32 2048^2, 1.3 times
-// the cache, 215k streaming, 203k cached), FP64 ones stream (8192^2 125.6k, cached 110.8k).
-StripLaunch strip_default(const Instance &in, size_t touched)
+// (FP32 8192^2 208k streaming / 220k cached, 4096^2 206k / 216k, FP16 8192^2 218k / 223k; 2048^2 FP32, 1.3
+// times the cache, 215k / 203k; the wider lines of the flux form's 48-column strips do not gain: 8192^2
+// 198k / 190k), FP64 ones stream (8192^2 125.6k / 110.8k).
+// FP32 periodic strips run at most three waves per SIMD, two from 7e6 nodes on: more of them spread the rows
+// in flight past L2 (8192^2 five waves 207k, three 214k, two 223k; below that the count is level).
+StripLaunch strip_default(const lbm_ctx *c, size_t touched, bool batch_fuses)
 {
     StripLaunch s;
+    const Instance &in = c->inst[0];
+    const bool f16 = is_f16_mode(in.mode);
+    if (c->inst.size() > 1) {
+        if (!batch_fuses || f16) return s;
+        for (const Instance &i : c->inst)
+            if (i.p.ny < 16) return s;
+        s.rows = kBatchStripRows;
+        return s;
+    }
     const int64_t nodes = (int64_t)in.p.nx * in.p.ny;
-    const bool f16 = is_f16_mode(in.mode), pairs = f16 && in.p.nx % 2 == 0 && nodes >= 12000000;
-    if (!fusable(in.p) || in.p.aux == LBM_AUX_FLUX || in.p.ny < 16 || in.lc.stores == 2) return s;
-    if (f16 && !pairs && (in.mode == MODE_F16SR_F32 || (in.p.nx <= 2048 && nodes >= fuse_min_nodes(in.mode)))) return s;
-    s.rows = pairs ? 48 : strip_rows(in.mode, in.p.nx, in.p.ny);
+    if (in.p.lattice != LBM_LATTICE_D2Q9 || in.p.boundary == LBM_BC_NEE || (in.p.tau3 != 0.0 && in.p.tau3 != 1.0) ||
+        in.p.ny < 16 || in.lc.stores == 2)
+        return s;
+    const bool walls = in.p.boundary == LBM_BC_WALLS, flux = in.p.aux == LBM_AUX_FLUX;
+    const bool pairs = f16 && !walls && !flux && in.p.nx % 2 == 0 && nodes >= 12000000;
+    if (in.mode == MODE_F16SR_F32 && !pairs) return s;
+    if (walls && in.mode == MODE_F64_F32) return s;
+    if (f16 && !pairs && !walls && in.p.nx <= 2048 && (in.p.nx + 511) / 512 * 512 - in.p.nx <= 64 && nodes >= fuse_min_nodes(in.mode))
+        return s;
+    s.rows = pairs ? 48 : strip_rows(in.mode, in.p.nx, in.p.ny, flux);
     s.cols = pairs ? 2 : 1;
-    s.cached = in.lc.stores == 1 || (store_bytes(in.mode) < 8 && touched > 2 * kInfinityCacheBytes);
+    if (in.mode == MODE_F32_F32 && !flux && !walls) s.lds_reserve = lds_reserve_for(nodes >= 7000000 ? 2 : 3, c->lds_per_cu);
+    s.cached = in.lc.stores == 1 || (store_bytes(in.mode) < 8 && !flux && touched > 2 * kInfinityCacheBytes);
     return s;
 }
 
@@ -710,9 +777,24 @@ int enqueue_fused(lbm_ctx *c, hipStream_t st)
     return LBM_OK;
 }
 
-// Enqueues kStripSteps steps of a context's one instance.
+// Steps of one strip launch.
+int strip_steps(const lbm_ctx *c) { return c->inst[0].p.aux == LBM_AUX_FLUX ? kFluxStripSteps : kStripSteps; }
+
+// Enqueues strip_steps steps of every instance.
 int enqueue_strips(lbm_ctx *c, hipStream_t st)
 {
+    if (c->inst.size() > 1) {
+        BatchArgs b;
+        b.inst = c->d_desc;
+        b.items = c->sched[2].d_items;
+        b.block_start = nullptr;
+        b.parity = c->parity;
+        b.one_row = 0;
+        hipError_t e = launch_batched_strips(c->inst[0].mode, c->inst[0].p.aux, b, c->strips.rows, c->sched[2].nblocks, st);
+        if (e != hipSuccess) return hip_fail(e, "batched strip kernel launch");
+        c->parity ^= 1;
+        return LBM_OK;
+    }
     StepArgs a;
     a.d = c->h_desc[0];
     a.parity = c->parity;
@@ -738,7 +820,7 @@ int graph_for(lbm_ctx *c, hipGraphExec_t *out)
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     int rc = LBM_OK;
     if (c->strips_on)
-        for (int t = 0; t < kGraphSteps / kStripSteps && rc == LBM_OK; ++t) rc = enqueue_strips(c, c->capture);
+        for (int t = 0; t < kGraphSteps / strip_steps(c) && rc == LBM_OK; ++t) rc = enqueue_strips(c, c->capture);
     else if (fused(c))
         for (int t = 0; t < kGraphSteps / 2 && rc == LBM_OK; ++t) rc = enqueue_fused(c, c->capture);
     else
@@ -945,16 +1027,11 @@ int lbm_init(lbm_ctx **out, int32_t n_inst, const lbm_params *p, const lbm_field
         }
         if (inplace) in.buf[1] = in.buf[0];
     }
-    if (n_inst == 1) {
-        c->strips = strip_default(i0, touched);
-        c->strips_on = c->strips.rows > 0;
-        lbm_get_launch(c, 0, &c->strips_with);
-    }
     const size_t items = max_items_of(n_inst, p);
     c->d_desc = reinterpret_cast<InstDesc *>(w);
     w += align_up((size_t)n_inst * sizeof(InstDesc), kAlign);
-    for (int j = 0; j < 2; ++j) {
-        const size_t ni = j == 0 ? items : (n_inst > 1 ? max_items2_of(n_inst, p) : 0);
+    for (int j = 0; j < 3; ++j) {
+        const size_t ni = j == 0 ? items : (n_inst == 1 ? 0 : (j == 1 ? max_items2_of(n_inst, p) : max_items3_of(n_inst, p)));
         c->sched[j].d_items = reinterpret_cast<WorkItem *>(w);
         w += align_up(ni * sizeof(WorkItem), kAlign);
         c->sched[j].d_block_start = reinterpret_cast<int32_t *>(w);
@@ -963,6 +1040,11 @@ int lbm_init(lbm_ctx **out, int32_t n_inst, const lbm_params *p, const lbm_field
     for (int k = 0; k < n_inst; ++k) c->inst[k].clock = reinterpret_cast<int64_t *>(w) + 2 * k;  // zeroed below
     // a uniform batch defaults to one flat launch; FP32 runs it with at most 6 waves per SIMD (+2 %)
     if (n_inst > 1 && c->uniform) c->batch = lbm_batch{LBM_BATCH_FLAT, 0, c->inst[0].mode == MODE_F32_F32 ? 6 : 0};
+
+    c->strips = strip_default(c, touched, batch_fuses);
+    c->strips_batch = c->batch;
+    lbm_get_launch(c, 0, &c->strips_with);
+    update_strips(c);
 
     // Zero everything the library owns (padding columns included) so that a state is a
     // deterministic byte image; this also clears the flags.
@@ -1055,7 +1137,7 @@ int lbm_step(lbm_ctx *c, int32_t nsteps, const double *const *ux, const double *
         }
     }
     if (c->strips_on)
-        for (; left >= kStripSteps; left -= kStripSteps) {
+        for (; left >= strip_steps(c); left -= strip_steps(c)) {
             rc = enqueue_strips(c, c->stream);
             if (rc) return account(rc);
         }
@@ -1292,11 +1374,7 @@ int lbm_set_launch(lbm_ctx *c, int32_t inst, const lbm_launch *cfg)
         else in.lc1.stores = lc.stores;
     }
     c->l2_streams = false;  // the caller's store kind holds for the adjoint's recomputation too
-    if (c->strips.rows > 0) {  // strips go with the default launch shape, and again with it
-        lbm_launch now = {};
-        lbm_get_launch(c, 0, &now);
-        c->strips_on = std::memcmp(&now, &c->strips_with, sizeof now) == 0;
-    }
+    update_strips(c);
     return refresh_tables(c);
 }
 
@@ -1331,6 +1409,7 @@ int lbm_set_batch(lbm_ctx *c, const lbm_batch *cfg)
     if (cfg->policy != LBM_BATCH_SERIAL && !c->uniform)
         return fail(LBM_E_UNSUPPORTED, "lbm_set_batch: instances differ in storage/arithmetic or aux form");
     c->batch = *cfg;
+    update_strips(c);
     return refresh_tables(c);
 }
 

@@ -200,16 +200,23 @@ hipError_t launch_step(int mode, int aux, const StepArgs &a, hipStream_t st);
 // buf[parity], writes buf[parity ^ 1] two steps later).  lcf.fuse_width columns x lcf.rows rows per tile.
 hipError_t launch_step2(int mode, int aux, const StepArgs &a, hipStream_t st);
 // kStripSteps steps per launch on strips of `rows` rows and `cols` columns per lane that one wave owns
-// (lbm_strips.h): periodic D2Q9 TRT-R, aux LOCAL or NONE, two buffers; cols 2 for FP16 storage and even nx.
+// (lbm_strips.h): D2Q9 TRT-R, two buffers, periodic (any aux term; the flux form kFluxStripSteps steps, not
+// with stochastic rounding) or between walls (aux LOCAL or NONE; not FP64 storage with FP32 math, not
+// stochastic rounding).  cols 2: FP16 storage, periodic, aux LOCAL or NONE, even nx.
 constexpr int kStripSteps = 4;
+constexpr int kFluxStripSteps = 4;
 // Output columns of a strip of NC columns per lane: each step takes one column off either end of a wave.
 constexpr int strip_width(int T, int NC) { return 64 * NC - 2 * T; }
 struct StripLaunch {
     int rows = 0;         // 0: the instance does not run on strips
     int cols = 1;
     bool cached = false;  // stores: as Launch::stores 1, else 0
+    int lds_reserve = 0;  // dynamic LDS bytes reserved per block to cap the resident waves (0: no cap)
 };
 hipError_t launch_strips(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
+// kStripSteps steps of many periodic instances in one launch (aux LOCAL or NONE, FP64 or FP32 storage): work
+// item i is strip `tile` (of `rows` rows) of instance `inst`; cached stores.
+hipError_t launch_batched_strips(int mode, int aux, const BatchArgs &a, int rows, int items, hipStream_t st);
 // The same for many instances in one launch: block b runs work items (instance, fused tile) as the
 // one-step batched kernel does; every instance has tiles of `width` columns (128, 256 or 512).
 hipError_t launch_batched_step2(int mode, int aux, const BatchArgs &a, int nblocks, int width, hipStream_t st);

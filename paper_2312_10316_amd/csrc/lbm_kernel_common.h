@@ -49,6 +49,25 @@ __device__ __forceinline__ void flux_aux(M pw, M pe, M ps, M pn, M uxw, M uyw, M
     Ay = (fex * uye - fwx * uyw) * M(0.5) + (fny * uyn - fsy * uys) * M(0.5) - uyc * div;
 }
 
+// The reflection at a wall (halfway anti-bounce-back): the node's own values p2, p5, p6 of the slots that
+// crossed it (4, 7, 8 at the bottom wall; 2, 5, 6 at the top one) come back in the opposite slots.
+template <class M>
+__device__ __forceinline__ void wall_reflect(M phiw, M ux, M uy, bool bottom, M p2, M p5, M p6, M (&g)[9])
+{
+    M e[9];
+    equilibrium<M>(phiw, ux, uy, e);
+    // every slot is written through a select (no slot-dependent branches), which keeps g in registers
+    const M a = (bottom ? e[2] + e[4] : e[4] + e[2]) - p2;
+    const M b = (bottom ? e[5] + e[7] : e[7] + e[5]) - p5;
+    const M c = (bottom ? e[6] + e[8] : e[8] + e[6]) - p6;
+    g[2] = bottom ? a : g[2];
+    g[5] = bottom ? b : g[5];
+    g[6] = bottom ? c : g[6];
+    g[4] = bottom ? g[4] : a;
+    g[7] = bottom ? g[7] : b;
+    g[8] = bottom ? g[8] : c;
+}
+
 // Time level of the state a launch reads (stochastic rounding only; 0 otherwise).  The counter pair
 // lives in device memory so that graph replays see the level advance: a launch reads clock[parity],
 // which no thread of it writes, and one thread of it writes clock[parity ^ 1] for the next launch.

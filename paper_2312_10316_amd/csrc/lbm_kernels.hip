@@ -88,22 +88,11 @@ __device__ __forceinline__ void wall_replace(const typename St::T *__restrict__ 
                                              M uy, bool bottom, const F16Params &f, int64_t pitch, M (&g)[9])
 {
     using C = Codec<St, M>;
-    M e[9];
-    equilibrium<M>(phiw, ux, uy, e);
-    // every slot is written through a select (no slot-dependent branches), which keeps g in registers
     const int o2 = bottom ? 4 : 2, o5 = bottom ? 7 : 5, o6 = bottom ? 8 : 6;  // stored slot reflected
     const M p2 = C::dec(ld_at(row + o2 * pitch, boff), o2, f);
     const M p5 = C::dec(ld_at(row + o5 * pitch, boff), o5, f);
     const M p6 = C::dec(ld_at(row + o6 * pitch, boff), o6, f);
-    const M a = (bottom ? e[2] + e[4] : e[4] + e[2]) - p2;
-    const M b = (bottom ? e[5] + e[7] : e[7] + e[5]) - p5;
-    const M c = (bottom ? e[6] + e[8] : e[8] + e[6]) - p6;
-    g[2] = bottom ? a : g[2];
-    g[5] = bottom ? b : g[5];
-    g[6] = bottom ? c : g[6];
-    g[4] = bottom ? g[4] : a;
-    g[7] = bottom ? g[7] : b;
-    g[8] = bottom ? g[8] : c;
+    wall_reflect<M>(phiw, ux, uy, bottom, p2, p5, p6, g);
 }
 
 // The state of node (x, y) as the step sees it before collision: the pull, then the boundary rule.
