@@ -236,6 +236,11 @@ hipError_t launch_adjoint(int mode, int aux, const AdjArgs &a, hipStream_t st);
 // D3Q19 and D3Q27 (lbm_kernels3d.hip, chosen by L.q): storage modes F64_F64, F64_F32, F32_F32; aux
 // LOCAL or NONE; periodic.
 hipError_t launch_step3(int mode, int aux, const StepArgs &a, hipStream_t st);
+// Two steps per launch on D3Q19 / D3Q27 (FP64 or FP32 storage): tiles of s.cols (at most 56) columns and
+// step3x2_waves - 2 rows that walk s.rows planes.  Waves of a block: the rows of FP32 fill the registers of
+// a CU with one block; FP64 takes six (256^3 4 % slower than eight, 100 x 100 x 80 18 % faster).
+constexpr int step3x2_waves(int q, int mode) { return mode == MODE_F64_F64 ? 6 : (q == 27 ? 12 : 16); }
+hipError_t launch_step3x2(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
 hipError_t launch_init3(int mode, const InitArgs &a, hipStream_t st);
 hipError_t launch_macros3(int mode, const MacroArgs &a, double *result, hipStream_t st);
 hipError_t launch_populations3(int mode, const PopArgs &a, hipStream_t st);

@@ -49,6 +49,31 @@ __device__ __forceinline__ void flux_aux(M pw, M pe, M ps, M pn, M uxw, M uyw, M
     Ay = (fex * uye - fwx * uyw) * M(0.5) + (fny * uyn - fsy * uys) * M(0.5) - uyc * div;
 }
 
+// The neighbouring lane's value: of lane - 1 (the columns to the west) and lane + 1 (east); the lanes at
+// the wave's ends, which have no such neighbour, get 0.
+template <int CTRL>
+__device__ __forceinline__ uint32_t lane_shift(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+constexpr int kFromWest = 0x138, kFromEast = 0x130;  // wave_shr:1, wave_shl:1
+template <int CTRL, class M>
+__device__ __forceinline__ M lane_value(M v)
+{
+    if constexpr (sizeof(M) == 8) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        return __builtin_bit_cast(M, (uint64_t)lane_shift<CTRL>((uint32_t)(b >> 32)) << 32 | lane_shift<CTRL>((uint32_t)b));
+    } else if constexpr (sizeof(M) == 4) {
+        return __builtin_bit_cast(M, lane_shift<CTRL>(__builtin_bit_cast(uint32_t, v)));
+    } else {
+        return __builtin_bit_cast(M, (uint16_t)lane_shift<CTRL>(__builtin_bit_cast(uint16_t, v)));
+    }
+}
+template <class M>
+__device__ __forceinline__ M lane_w(M v) { return lane_value<kFromWest>(v); }
+template <class M>
+__device__ __forceinline__ M lane_e(M v) { return lane_value<kFromEast>(v); }
+
 // The reflection at a wall (halfway anti-bounce-back): the node's own values p2, p5, p6 of the slots that
 // crossed it (4, 7, 8 at the bottom wall; 2, 5, 6 at the top one) come back in the opposite slots.
 template <class M>

@@ -332,6 +332,245 @@ __global__ __launch_bounds__(256) void step3_kernel(const StepArgs sa)
     }
 }
 
+// ---- two steps per launch ---------------------------------------------------------------------------
+//
+// Slot of the LDS exchange of velocity i, which moves along y (others: -1).
+template <int Q>
+__host__ __device__ constexpr int yslot(int i)
+{
+    if (kEy3[i] == 0) return -1;
+    int n = 0;
+    for (int j = 0; j < i; ++j) n += kEy3[j] != 0;
+    return n;
+}
+template <int Q>
+__host__ __device__ constexpr int yslots()
+{
+    int n = 0;
+    for (int j = 0; j < Q; ++j) n += kEy3[j] != 0;
+    return n;
+}
+
+// A block of NW waves owns NW adjacent lattice rows (one per wave, wrapped) of 64 columns (lane = column)
+// and walks `planes` output planes in z.  Iteration k computes step 1 of plane z = z0 - 1 + k for all its
+// rows (from the state in memory, loaded one plane ahead) and, one plane behind, step 2 of plane z - 1 for
+// the inner NW - 2 rows and the `width` inner columns, which it stores.  Between the steps the populations
+// stay on chip: those moving along y go to the neighbouring waves through LDS (two buffers, one barrier per
+// plane), those moving along x only come from the neighbouring lanes, and what moves with the walk or stays
+// in the plane waits in registers (e_z = 0 one plane, e_z = +1 two).  Per node the arithmetic is that of
+// step3_kernel, so two steps are bitwise two launches of it.
+//
+// What bounds it: the one-step kernel is bound by memory (256^3 FP32 6.1 TB/s); this one moves half the bytes
+// and issues vector instructions 53 % of the time (D3Q19 FP32; 640 per two node updates), the rest being
+// the plane's barrier with one block per CU.  Times per step, one / two steps per launch: D3Q19 256^3 FP32
+// 453 / 365 us, FP64 955 / 703, D3Q27 FP32 638 / 550, FP64 1323 / 952; 100 x 100 x 80 D3Q19 FP32 25.9 / 20.1,
+// FP64 60.5 / 38.6, D3Q27 FP32 36.5 / 27.2, FP64 73.2 / 53.2.  FP16 storage is not built: its codec makes the
+// recomputed rows and lanes cost more than the bytes saved (D3Q19 256^3 259 / 291 us).
+template <int Q, int MODE, int AUX, bool HAS_K, bool HAS_S, int NW, bool CST>
+__global__ __launch_bounds__(64 * NW) void step3x2_kernel(const StepArgs sa, const int width, const int planes)
+{
+    using St = typename ModeTraits<MODE>::St;
+    using M = typename ModeTraits<MODE>::M;
+    using E = typename St::T;
+    using C = Codec<St, M>;
+    static_assert(!is_f16_mode(MODE), "a step-1 value passes its codec unchanged");
+    constexpr int NS = yslots<Q>();
+    __shared__ M xch[2 * NS * NW * 64 + 2];  // one spare element at either end (lanes without a neighbour)
+    const InstDesc &a = sa.d;
+    const int nx = a.L.nx, ny = a.L.ny, nz = a.L.nz;
+    const int64_t pitch = a.L.pitch;
+    const F16Params &f = a.f16;
+    const int nsx = (nx + width - 1) / width, nty = (ny + NW - 3) / (NW - 2);
+    const int t = tile_of_block(blockIdx.x, gridDim.x, 1, 0, 0);
+    const int tz = t / (nsx * nty), txy = t - tz * nsx * nty, ty = txy / nsx;
+    const int xs = (txy - ty * nsx) * width, y0 = ty * (NW - 2), z0 = tz * planes, z1 = min(z0 + planes, nz);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63u);
+    const int G = (64 - width) >> 1;  // columns beyond the output on either side (at least two are needed)
+    int xi = (xs - G + lane) % nx;
+    xi = xi < 0 ? xi + nx : xi;
+    const int yw = y0 - 1 + w, y = (yw + ny) % ny;
+    const bool outrow = w > 0 && w < NW - 1 && yw < ny;
+    const bool live = lane >= G && lane < G + width && xs + lane - G < nx;
+    const int ym = wrap_dec(y, ny), yp = wrap_inc(y, ny);
+    const unsigned xm = xi == 0 ? (unsigned)nx - 1 : (unsigned)xi - 1, xp = xi == nx - 1 ? 0u : (unsigned)xi + 1;
+    unsigned bc = (unsigned)xi * (unsigned)sizeof(E), bm = xm * (unsigned)sizeof(E), bp = xp * (unsigned)sizeof(E);
+    unsigned fc = (unsigned)xi * (unsigned)sizeof(M);
+    const E *__restrict__ src = static_cast<const E *>(a.buf[sa.parity]);
+    E *__restrict__ dst = static_cast<E *>(a.buf[sa.parity ^ 1]);
+    const M *__restrict__ u = static_cast<const M *>(a.u);
+    const M *__restrict__ kf = static_cast<const M *>(a.k);
+    const M *__restrict__ sf = static_cast<const M *>(a.s);
+    Relax<M> rconst;
+    rconst.w1 = (M)a.w1;
+    rconst.w2 = (M)a.w2;
+    rconst.beta = (M)a.beta;
+    rconst.w3 = M(0);
+
+    int zm = (z0 - 2 + nz) % nz, zc = wrap_inc(zm, nz), zp = wrap_inc(zc, nz);  // planes z - 1, z, z + 1
+    struct Loads {
+        E g[Q];
+        M up[3], un[3], us[3], k, s;  // u of (y, z + 1), (y + 1, z), (y - 1, z)
+    };
+    auto fetch = [&](Loads &o) {
+        asm volatile("" : "+v"(bc), "+v"(bm), "+v"(bp), "+v"(fc));  // keeps scalar bases + 32-bit lane offsets
+        const int a0 = __builtin_amdgcn_readfirstlane(zm), a1 = __builtin_amdgcn_readfirstlane(zc),
+                  a2 = __builtin_amdgcn_readfirstlane(zp);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int yy = kEy3[i] > 0 ? ym : (kEy3[i] < 0 ? yp : y), zz = kEz3[i] > 0 ? a0 : (kEz3[i] < 0 ? a2 : a1);
+            const E *__restrict__ b = src + (((int64_t)zz * ny + yy) * Q + i) * pitch;
+            o.g[i] = ld_at(b, kEx3[i] > 0 ? bm : (kEx3[i] < 0 ? bp : bc));
+        }
+        const M *__restrict__ vp = u + ((int64_t)a2 * ny + y) * 3 * pitch;
+        const M *__restrict__ vn = u + ((int64_t)a1 * ny + yp) * 3 * pitch;
+        const M *__restrict__ vs = u + ((int64_t)a1 * ny + ym) * 3 * pitch;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            o.up[c] = ld_at(vp + c * pitch, fc);
+            if (AUX == 0) {
+                o.un[c] = ld_at(vn + c * pitch, fc);
+                o.us[c] = ld_at(vs + c * pitch, fc);
+            }
+        }
+        if (HAS_K) o.k = ld_at(kf + ((int64_t)a1 * ny + y) * pitch, fc);
+        if (HAS_S) o.s = ld_at(sf + ((int64_t)a1 * ny + y) * pitch, fc);
+    };
+    M ub[3], uc[3];  // u of planes z - 1 and z
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        ub[c] = ld_at(u + (((int64_t)zm * ny + y) * 3 + c) * pitch, fc);
+        uc[c] = ld_at(u + (((int64_t)zc * ny + y) * 3 + c) * pitch, fc);
+    }
+    Loads nxt;
+    fetch(nxt);
+    // of plane z - 1: u_b d_b u_a, u, the relaxation and the source; step-1 values as step 2 pulls them: of
+    // plane z - 1 those with e_z = 0 (e0) and e_z = 1 (p1), of plane z - 2 those with e_z = 1 (p2)
+    M ddm[3] = {M(0), M(0), M(0)}, um[3] = {M(0), M(0), M(0)}, sm = M(0);
+    Relax<M> rm = rconst;
+    M e0[Q], p1[Q], p2[Q];
+    const int nk = z1 - z0 + 2;
+#pragma unroll 1
+    for (int k = 0; k < nk; ++k) {
+        const Loads cur = nxt;
+        zm = zc;
+        zc = zp;
+        zp = wrap_inc(zp, nz);
+        fetch(nxt);
+        // ---- step 1 of plane z ----
+        M dd[3] = {M(0), M(0), M(0)};
+        if (AUX == 0) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const M dxc = lane_e(uc[c]) - lane_w(uc[c]);
+                const M dyc = cur.un[c] - cur.us[c];
+                const M dzc = cur.up[c] - ub[c];
+                dd[c] = M(0.5) * (uc[0] * dxc + uc[1] * dyc + uc[2] * dzc);
+            }
+        }
+        const Relax<M> rr = HAS_K ? relax_from_k<M>(cur.k, (M)a.lambda, M(0)) : rconst;
+        const M s = HAS_S ? cur.s : M(0);
+        M o[Q];  // (FP64 and FP32 storage decode what they encode unchanged)
+        {
+            M g[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) g[i] = C::dec(cur.g[i], i, f);
+            M Ax = M(0), Ay = M(0), Az = M(0);
+            if (AUX == 0) {
+                M phi = g[0];
+#pragma unroll
+                for (int i = 1; i < Q; ++i) phi += g[i];
+                Ax = phi * dd[0];
+                Ay = phi * dd[1];
+                Az = phi * dd[2];
+            }
+            collide3<Q, M>(g, uc[0], uc[1], uc[2], rr, Ax, Ay, Az, s, o);
+        }
+        M *const xb = xch + 1 + (k & 1) * (NS * NW * 64);
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            if (yslot<Q>(i) >= 0) xb[(yslot<Q>(i) * NW + w) * 64 + lane] = o[i];
+        __syncthreads();
+        // the step-1 values of plane z at (x - e_x, y - e_y)
+        M v[Q];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            if (yslot<Q>(i) >= 0) {
+                const int ws = kEy3[i] > 0 ? max(w - 1, 0) : min(w + 1, NW - 1);
+                v[i] = xb[(yslot<Q>(i) * NW + ws) * 64 + lane - kEx3[i]];
+            } else {
+                v[i] = kEx3[i] > 0 ? lane_w(o[i]) : (kEx3[i] < 0 ? lane_e(o[i]) : o[i]);
+            }
+        }
+        // ---- step 2 of plane z - 1 ----
+        if (k >= 2 && outrow) {
+            M g[Q], P[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                g[i] = kEz3[i] == 0 ? e0[i] : (kEz3[i] > 0 ? p2[i] : v[i]);
+            }
+            M Ax = M(0), Ay = M(0), Az = M(0);
+            if (AUX == 0) {
+                M phi = g[0];
+#pragma unroll
+                for (int i = 1; i < Q; ++i) phi += g[i];
+                Ax = phi * ddm[0];
+                Ay = phi * ddm[1];
+                Az = phi * ddm[2];
+            }
+            collide3<Q, M>(g, um[0], um[1], um[2], rm, Ax, Ay, Az, sm, P);
+            if (live) {
+                E *__restrict__ out = dst + ((int64_t)__builtin_amdgcn_readfirstlane(z0 + k - 2) * ny + y) * Q * pitch;
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    if constexpr (CST) st_at(out + i * pitch, bc, C::enc(P[i], i, f));
+                    else st_nt_at(out + i * pitch, bc, C::enc(P[i], i, f));
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            p2[i] = p1[i];
+            p1[i] = v[i];
+            e0[i] = v[i];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            ddm[c] = dd[c];
+            um[c] = uc[c];
+            ub[c] = uc[c];
+            uc[c] = cur.up[c];
+        }
+        rm = rr;
+        sm = s;
+    }
+}
+
+template <int Q, int MODE, int AUX, bool CST>
+hipError_t launch_step3x2_st(const StepArgs &a, const StripLaunch &s, hipStream_t st)
+{
+    constexpr int NW = step3x2_waves(Q, MODE);
+    const Layout &L = a.d.L;
+    const int64_t nb = (int64_t)((L.nx + s.cols - 1) / s.cols) * ((L.ny + NW - 3) / (NW - 2)) * ((L.nz + s.rows - 1) / s.rows);
+    if (nb > INT32_MAX / 64) return hipErrorInvalidValue;
+    const bool hk = a.d.has_k, hs = a.d.has_s;
+    if (hk && hs) step3x2_kernel<Q, MODE, AUX, true, true, NW, CST><<<(int)nb, 64 * NW, 0, st>>>(a, s.cols, s.rows);
+    else if (hk) step3x2_kernel<Q, MODE, AUX, true, false, NW, CST><<<(int)nb, 64 * NW, 0, st>>>(a, s.cols, s.rows);
+    else if (hs) step3x2_kernel<Q, MODE, AUX, false, true, NW, CST><<<(int)nb, 64 * NW, 0, st>>>(a, s.cols, s.rows);
+    else step3x2_kernel<Q, MODE, AUX, false, false, NW, CST><<<(int)nb, 64 * NW, 0, st>>>(a, s.cols, s.rows);
+    return hipGetLastError();
+}
+
+template <int Q, int MODE>
+hipError_t launch_step3x2_mode(int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st)
+{
+    switch (aux) {
+    case 0: return s.cached ? launch_step3x2_st<Q, MODE, 0, true>(a, s, st) : launch_step3x2_st<Q, MODE, 0, false>(a, s, st);
+    case 2: return s.cached ? launch_step3x2_st<Q, MODE, 2, true>(a, s, st) : launch_step3x2_st<Q, MODE, 2, false>(a, s, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 template <int Q, int MODE>
 __global__ __launch_bounds__(256) void init3_kernel(const InitArgs a)
 {
@@ -501,6 +740,19 @@ hipError_t launch_step3(int mode, int aux, const StepArgs &a, hipStream_t st)
         return q27 ? launch_step3_mode<27, MODE_F32_F32>(aux, a, st) : launch_step3_mode<19, MODE_F32_F32>(aux, a, st);
     case MODE_F16S_F32:
         return q27 ? launch_step3_mode<27, MODE_F16S_F32>(aux, a, st) : launch_step3_mode<19, MODE_F16S_F32>(aux, a, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_step3x2(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st)
+{
+    if ((a.d.L.q != 19 && a.d.L.q != 27) || a.d.buf[0] == a.d.buf[1] || s.rows < 1 || s.cols < 1 || s.cols > 56)
+        return hipErrorInvalidValue;
+    const bool q27 = a.d.L.q == 27;
+    switch (mode) {
+    case MODE_F64_F64: return q27 ? launch_step3x2_mode<27, MODE_F64_F64>(aux, a, s, st) : launch_step3x2_mode<19, MODE_F64_F64>(aux, a, s, st);
+    case MODE_F64_F32: return q27 ? launch_step3x2_mode<27, MODE_F64_F32>(aux, a, s, st) : launch_step3x2_mode<19, MODE_F64_F32>(aux, a, s, st);
+    case MODE_F32_F32: return q27 ? launch_step3x2_mode<27, MODE_F32_F32>(aux, a, s, st) : launch_step3x2_mode<19, MODE_F32_F32>(aux, a, s, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -39,15 +39,6 @@
 namespace lbm {
 namespace {
 
-// The neighbouring lane's value: of lane - 1 (the columns to the west) and lane + 1 (east); the lanes at
-// the wave's ends, which have no such neighbour, get 0.
-template <int CTRL>
-__device__ __forceinline__ uint32_t lane_shift(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
-}
-constexpr int kFromWest = 0x138, kFromEast = 0x130;  // wave_shr:1, wave_shl:1
-
 // The values of NC adjacent columns, which one lane owns.
 template <class E, int NC>
 struct Cols {
@@ -80,10 +71,6 @@ __device__ __forceinline__ Cols<E, NC> east_of(Cols<E, NC> p)
     else if constexpr (sizeof(E) == 4) return {p.v[1], __builtin_bit_cast(E, lane_shift<kFromEast>(__builtin_bit_cast(uint32_t, p.v[0])))};
     else return {p.v[1], shift_words<kFromEast>(p).v[0]};
 }
-template <class M>
-__device__ __forceinline__ M lane_w(M v) { return west_of(Cols<M, 1>{v}).v[0]; }
-template <class M>
-__device__ __forceinline__ M lane_e(M v) { return east_of(Cols<M, 1>{v}).v[0]; }
 template <class E, int NC>
 __device__ __forceinline__ Cols<E, NC> ld_cols(const E *base, unsigned byte_off)
 {
@@ -403,7 +390,7 @@ __device__ __forceinline__ void strip_walk(const InstDesc &d, int parity, int xs
     for (int k = 0; k < nk; ++k) row(std::false_type{}, k, 0);
     constexpr std::true_type all{};
     int y = UP ? y1 - 1 : y0;
-    if constexpr (NC == 1) {  // unrolled by two: the rolled values are renamed, not copied
+    if constexpr (MODE != MODE_F16SR_F32) {  // unrolled by two: the rolled values are renamed, not copied
         int left = y1 - y0;
         for (; left > 1; left -= 2) {
             row(all, nk, y);
@@ -411,7 +398,7 @@ __device__ __forceinline__ void strip_walk(const InstDesc &d, int parity, int xs
             y += 2 * dir;
         }
         if (left) row(all, nk, y);
-    } else {  // unrolled, two columns per lane would not fit 256 registers
+    } else {  // the rounding's values spill when unrolled (8192^2 with D 149k -> 130k MLUPS)
 #pragma unroll 1
         for (int left = y1 - y0; left > 0; --left, y += dir) row(all, nk, y);
     }
