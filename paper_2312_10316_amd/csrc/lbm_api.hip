@@ -341,6 +341,10 @@ struct Instance {
     char *buf[2];
     char *alt;   // the workspace's second population buffer (buf[1] unless the instance runs in place)
     void *u, *k, *s, *bc;
+    lbm_launch shape;  // the default launch shape as reported
+    bool flat_ok;      // single steps of that shape run on the gapless 3D kernel
+    bool one_ok;       // that shape (two buffers) runs on one buffer in place
+    bool one_on;       // it is set, and does
     bool has_D;
     bool has_src;
     int64_t step;
@@ -475,9 +479,8 @@ struct lbm_ctx {
     int parity = 0;                   // the buffer every instance currently reads (they step together)
     bool uniform = false;             // all instances share mode and aux (a batched launch is possible)
     StripLaunch strips;               // several steps per launch on strips (rows 0: never)
-    lbm_launch strips_with = {};      // the launch shape the strips belong to (the default one)
-    lbm_batch strips_batch = {};      // and the batch schedule
-    bool strips_on = false;           // every instance has that shape, and the context that schedule
+    lbm_batch strips_batch = {};      // the default batch schedule
+    bool strips_on = false;           // that schedule and every instance's default shape are set: strips run
     bool l2_streams = false;          // steps stream their stores although the state fits the caches
     lbm_batch batch = {LBM_BATCH_SERIAL, 0, 0};
     InstDesc *d_desc = nullptr;       // device tables (in the workspace)
@@ -604,15 +607,36 @@ int build_strip_schedule(lbm_ctx *c)
     return e == hipSuccess ? LBM_OK : hip_fail(e, "uploading strip work items");
 }
 
-// Strips go with the default launch shape and batch schedule, and again when the caller sets those.
+// Strips and the gapless 3D kernel go with the default launch shape (and batch schedule), and again when the
+// caller sets those.
 void update_strips(lbm_ctx *c)
 {
     c->strips_on = c->strips.rows > 0 && std::memcmp(&c->batch, &c->strips_batch, sizeof c->batch) == 0;
-    for (int k = 0; k < (int)c->inst.size() && c->strips_on; ++k) {
+    for (int k = 0; k < (int)c->inst.size(); ++k) {
+        Instance &in = c->inst[k];
         lbm_launch now = {};
         lbm_get_launch(c, k, &now);
-        c->strips_on = std::memcmp(&now, &c->strips_with, sizeof now) == 0;
+        const bool same = std::memcmp(&now, &in.shape, sizeof now) == 0;
+        c->strips_on = c->strips_on && same;
+        in.lc.flat = in.lc1.flat = same && in.flat_ok ? 1 : 0;
     }
+}
+
+// Lattices whose single steps run on the gapless 3D kernel in their default launch shape: with row tiles more
+// than a quarter of the lanes would be idle, cached stores, at least 32 columns (a wave then spans at most
+// three rows), and 32-bit offsets.  (100 to 200 columns measured level or, FP16 D3Q27, 12 % slower.)
+bool flat_default(const Instance &in)
+{
+    return is3d(in) && in.lc.stores == 1 && in.p.nx >= 32 && (in.p.nx + 63) / 64 * 64 > 1.34 * in.p.nx &&
+           pops_bytes(in.p) <= UINT32_MAX && vel_bytes(in.p) <= UINT32_MAX;
+}
+
+// Bytes of the cache lines (128 B) that a 3D instance's steps touch with `bufs` population buffers: rows of a
+// few lines waste much of the last one (68 columns FP32: 272 of 384 bytes).
+size_t lines_touched(const Instance &in, int bufs)
+{
+    const auto row = [&](size_t elem) { return align_up((size_t)in.L.nx * elem, 128); };
+    return (size_t)rows_of(in.L) * (bufs * in.L.q * row(store_bytes(in.mode)) + (dim_of(in.L) + (in.has_D ? 1 : 0)) * row(math_bytes(in.mode)));
 }
 
 // Rebuilds the descriptors and (for a batched policy) the work list, and uploads them.  The host
@@ -637,6 +661,14 @@ int refresh_tables(lbm_ctx *c)
     return e == hipSuccess ? LBM_OK : hip_fail(e, "synchronizing after a table update");
 }
 
+// A context of one 3D instance that runs in place in its default launch shape, though that has two buffers.
+bool one_buffer_3d(const lbm_ctx *c)
+{
+    const Instance &in = c->inst[0];
+    return is3d(in) && in.lc.stores != 2 && in.lc.rows == 1 && in_place_ok(in.p, in.mode, (int)c->inst.size()) &&
+           lines_touched(in, 2) > kInfinityCacheBytes && lines_touched(in, 1) <= kInfinityCacheBytes;
+}
+
 // Two steps per launch of one D3Q19 or D3Q27 instance (rows: planes per tile; cols: columns), or rows 0.
 // Columns: a multiple of eight up to 56, so that tiles start on 32-byte boundaries (60 columns at 240 x 224 x
 // 128 D3Q19 FP32 10.5 us per plane of a CU, 48 columns 6.4 us).  Planes: fewest iterations over the
@@ -647,10 +679,11 @@ int refresh_tables(lbm_ctx *c)
 // Stores: cached within the Infinity Cache, and where a tile's row ends inside a 64-byte block, which
 // neighbouring tiles then merge (256^3 FP32, 56 columns, 365 us cached, 383 streaming; 48 columns at 240 x
 // 224 x 128 189 and 173; FP64 256^3 731 and 704).
-StripLaunch planes_default(const Instance &in)
+StripLaunch planes_default(const lbm_ctx *c)
 {
     StripLaunch s;
-    if (is_f16_mode(in.mode) || in.lc.stores == 2) return s;
+    const Instance &in = c->inst[0];
+    if ((in.mode != MODE_F64_F64 && in.mode != MODE_F32_F32) || in.lc.stores == 2) return s;
     const Layout &L = in.L;
     const int ns = (L.nx + 55) / 56;
     s.cols = std::min(56, ((L.nx + ns - 1) / ns + 7) / 8 * 8);
@@ -665,7 +698,7 @@ StripLaunch planes_default(const Instance &in)
     }
     const bool f64 = in.mode == MODE_F64_F64;
     const double two = 1.0 + (double)least * (f64 ? (L.q == 27 ? 5.7 : 4.2) : (L.q == 27 ? 6.0 : 6.2)) / 2.0;
-    const double one = 2.0 + (double)L.nx * L.ny * L.nz * (2.0 * L.q * store_bytes(in.mode) + 3.0 * math_bytes(in.mode)) / 5.6e6;
+    const double one = one_buffer_3d(c) ? 2.0 + (double)lines_touched(in, 1) * 2.0 / 6.5e6 : 2.0 + (double)L.nx * L.ny * L.nz * (2.0 * L.q * store_bytes(in.mode) + 3.0 * math_bytes(in.mode)) / 5.6e6;
     if (two > 0.95 * one) return StripLaunch{};
     s.cached = in.lc.stores == 1 || (s.cols * store_bytes(in.mode)) % 64 != 0;
     return s;
@@ -701,7 +734,7 @@ StripLaunch strip_default(const lbm_ctx *c, size_t touched, bool batch_fuses)
         s.rows = kBatchStripRows;
         return s;
     }
-    if (is3d(in)) return planes_default(in);
+    if (is3d(in)) return planes_default(c);
     const int64_t nodes = (int64_t)in.p.nx * in.p.ny;
     if (in.p.lattice != LBM_LATTICE_D2Q9 || in.p.boundary == LBM_BC_NEE || (in.p.tau3 != 0.0 && in.p.tau3 != 1.0) ||
         in.p.ny < 16 || in.lc.stores == 2)
@@ -1081,8 +1114,26 @@ int lbm_init(lbm_ctx **out, int32_t n_inst, const lbm_params *p, const lbm_field
     if (n_inst > 1 && c->uniform) c->batch = lbm_batch{LBM_BATCH_FLAT, 0, c->inst[0].mode == MODE_F32_F32 ? 6 : 0};
 
     c->strips_batch = c->batch;
-    lbm_get_launch(c, 0, &c->strips_with);
+    for (int k = 0; k < n_inst; ++k) {
+        c->inst[k].shape = {};
+        lbm_get_launch(c, k, &c->inst[k].shape);
+    }
     c->strips = strip_default(c, touched, batch_fuses);
+    // A 3D instance whose two buffers exceed the Infinity Cache only by the unused parts of their cache lines,
+    // or one buffer of which fits with them, runs in place as well (same results and state images; the
+    // reported shape stays): D3Q19 FP32 68 x 123 x 172 63 -> 45 us per step, D3Q27 FP16 150 x 130 x 110 67 -> 50,
+    // D3Q19 FP16 129 x 128 x 128 56 -> 40.
+    Instance &in0 = c->inst[0];
+    if (c->strips.rows == 0 && one_buffer_3d(c)) {
+        in0.one_ok = in0.one_on = true;
+        in0.buf[1] = in0.buf[0];
+        in0.lc.stores = in0.lc1.stores = 2;
+        in0.lc.xcd_remap = in0.lc1.xcd_remap = 1;
+        in0.lc.xcd_rows = in0.lc1.xcd_rows = 0;
+        in0.lc.max_waves = in0.lc1.max_waves = 0;
+        in0.lc.lds_reserve = in0.lc1.lds_reserve = 0;
+    }
+    for (Instance &in : c->inst) in.flat_ok = flat_default(in);
     update_strips(c);
 
     // Zero everything the library owns (padding columns included) so that a state is a
@@ -1343,6 +1394,12 @@ int lbm_set_launch(lbm_ctx *c, int32_t inst, const lbm_launch *cfg)
     if (!c || inst < -1 || inst >= (int32_t)c->inst.size())
         return fail(LBM_E_STATE, "lbm_set_launch: bad context or instance %d", inst);
     if (!cfg) return fail(LBM_E_ARG, "lbm_set_launch: cfg is NULL");
+    lbm_launch one = *cfg;  // the default shape of an instance that then runs on one buffer in place
+    const bool hide = c->inst[0].one_ok && std::memcmp(cfg, &c->inst[0].shape, sizeof *cfg) == 0;
+    if (hide) {
+        one.stores = 2;
+        cfg = &one;
+    }
     if (cfg->fuse < 0 || cfg->fuse > 2) return fail(LBM_E_ARG, "lbm_set_launch: fuse=%d must be 0, 1 or 2", cfg->fuse);
     const bool two = cfg->fuse == 2;
     const int max_rows = two ? 256 : 64;
@@ -1413,6 +1470,7 @@ int lbm_set_launch(lbm_ctx *c, int32_t inst, const lbm_launch *cfg)
         else in.lc1.stores = lc.stores;
     }
     c->l2_streams = false;  // the caller's store kind holds for the adjoint's recomputation too
+    c->inst[0].one_on = hide;
     update_strips(c);
     return refresh_tables(c);
 }
@@ -1422,6 +1480,10 @@ int lbm_get_launch(lbm_ctx *c, int32_t inst, lbm_launch *cfg)
     g_err[0] = 0;
     if (!check_inst(c, inst)) return fail(LBM_E_STATE, "lbm_get_launch: bad context or instance %d", inst);
     if (!cfg) return fail(LBM_E_ARG, "lbm_get_launch: cfg is NULL");
+    if (c->inst[inst].one_on) {
+        *cfg = c->inst[inst].shape;
+        return LBM_OK;
+    }
     const Launch &lc = c->inst[inst].lc;
     const bool two = lc.fuse == 2;
     cfg->rows = lc.rows;

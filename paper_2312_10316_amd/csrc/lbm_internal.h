@@ -58,7 +58,7 @@ struct Launch {
     int32_t stores;       // 0: non-temporal stores of the new state; 1: cached; 2: one buffer in place, cached
     int32_t fuse;         // time steps per launch: 1 (0 reads as 1), or 2 (step2_kernel, lbm_fused.hip)
     int32_t fuse_width;   // fused launches: output columns per tile (128, 256 or 512); rows = tile height
-    int32_t pad_;
+    int32_t flat;         // 3D one-step launches: nodes dealt to the lanes without gaps (step3_flat_kernel)
 };
 
 // Everything a step kernel needs about one instance.  Single-instance launches pass it by value;
@@ -236,7 +236,7 @@ hipError_t launch_adjoint(int mode, int aux, const AdjArgs &a, hipStream_t st);
 // D3Q19 and D3Q27 (lbm_kernels3d.hip, chosen by L.q): storage modes F64_F64, F64_F32, F32_F32; aux
 // LOCAL or NONE; periodic.
 hipError_t launch_step3(int mode, int aux, const StepArgs &a, hipStream_t st);
-// Two steps per launch on D3Q19 / D3Q27 (FP64 or FP32 storage): tiles of s.cols (at most 56) columns and
+// Two steps per launch on D3Q19 / D3Q27 (FP64, or FP32 storage): tiles of s.cols (at most 56) columns and
 // step3x2_waves - 2 rows that walk s.rows planes.  Waves of a block: the rows of FP32 fill the registers of
 // a CU with one block; FP64 takes six (256^3 4 % slower than eight, 100 x 100 x 80 18 % faster).
 constexpr int step3x2_waves(int q, int mode) { return mode == MODE_F64_F64 ? 6 : (q == 27 ? 12 : 16); }

@@ -332,6 +332,90 @@ __global__ __launch_bounds__(256) void step3_kernel(const StepArgs sa)
     }
 }
 
+// One step with the lattice's nodes dealt to the lanes row by row without gaps: a wave takes 64 consecutive
+// nodes of the sequence (z, y, x), which span up to three lattice rows (nx >= 32).  step3_kernel's waves each
+// cover 64 columns of one row, so a row whose length is not a multiple of 64 leaves lanes idle (68 columns:
+// 60 of 128); here every lane works, at the cost of per-lane row offsets (about 60 vector instructions on
+// kernels whose time goes to memory).  A lane's accesses are scalar bases plus 32-bit byte offsets, so the
+// state must be smaller than 4 GiB.  Cached stores (a wave's segments start inside cache lines, which streaming
+// stores write in parts: D3Q19 FP16 250^3 274 -> 366 us).  The same arithmetic, bitwise.  Per step, row tiles /
+// gapless: D3Q19 FP32 45 x 200 x 100 33.2 / 22.6 us, FP16 45 x 50 x 60 6.9 / 6.3, D3Q27 FP32 70 x 60 x 40
+// 13.0 / 9.8, FP64 40 x 50 x 60 13.6 / 11.0.
+template <int Q, int MODE, int AUX, bool HAS_K, bool HAS_S>
+__global__ __launch_bounds__(256) void step3_flat_kernel(const StepArgs sa)
+{
+    using St = typename ModeTraits<MODE>::St;
+    using M = typename ModeTraits<MODE>::M;
+    using T = typename St::T;
+    using C = Codec<St, M>;
+    const InstDesc &a = sa.d;
+    const F16Params &f = a.f16;
+    const int nx = a.L.nx, ny = a.L.ny, nz = a.L.nz;
+    const int64_t pitch = a.L.pitch;
+    const unsigned total = (unsigned)((int64_t)nx * ny * nz);
+    const unsigned t = (unsigned)tile_of_block(blockIdx.x, gridDim.x, a.lc.xcd_remap == 1 ? 1 : 0, 0, 0);
+    const unsigned n0 = t * 256u + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * 64u;
+    if (n0 >= total) return;
+    const int lane = (int)(threadIdx.x & 63u);
+    const bool live = n0 + (unsigned)lane < total;  // the last wave's other lanes run on and store nothing
+    const int r0 = (int)(n0 / (unsigned)nx), z0 = r0 / ny, y0 = r0 - z0 * ny;
+    int x = (int)(n0 - (unsigned)r0 * (unsigned)nx) + lane, y = y0, z = z0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const bool over = x >= nx;
+        x = over ? x - nx : x;
+        y = over ? y + 1 : y;
+        const bool up = y == ny;
+        y = up ? 0 : y;
+        z = up ? wrap_inc(z, nz) : z;
+    }
+    const unsigned xm = x == 0 ? (unsigned)nx - 1 : (unsigned)x - 1, xp = x == nx - 1 ? 0u : (unsigned)x + 1;
+    const int ym = wrap_dec(y, ny), yp = wrap_inc(y, ny), zm = wrap_dec(z, nz), zp = wrap_inc(z, nz);
+    auto row = [&](int dy, int dz) { return (unsigned)((dz < 0 ? zm : (dz > 0 ? zp : z)) * ny + (dy < 0 ? ym : (dy > 0 ? yp : y))); };
+    const unsigned pb = (unsigned)(Q * pitch) * (unsigned)sizeof(T), fb = (unsigned)(3 * pitch) * (unsigned)sizeof(M);
+    auto col = [&](int dx) { return dx < 0 ? xm : (dx > 0 ? xp : (unsigned)x); };
+    // byte offset of the node x + (dx, dy, dz) within slot 0 of its row
+    auto at = [&](int dx, int dy, int dz) { return row(dy, dz) * pb + col(dx) * (unsigned)sizeof(T); };
+    auto uat = [&](int dx, int dy, int dz) { return row(dy, dz) * fb + col(dx) * (unsigned)sizeof(M); };
+    const T *__restrict__ src = static_cast<const T *>(a.buf[sa.parity]);
+    T *__restrict__ dst = static_cast<T *>(a.buf[sa.parity ^ 1]);
+    const M *__restrict__ u = static_cast<const M *>(a.u);
+    M g[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) g[i] = C::dec(ld_at(src + i * pitch, at(-kEx3[i], -kEy3[i], -kEz3[i])), i, f);
+    const M ux = ld_at(u, uat(0, 0, 0)), uy = ld_at(u + pitch, uat(0, 0, 0)), uz = ld_at(u + 2 * pitch, uat(0, 0, 0));
+    M Ax = M(0), Ay = M(0), Az = M(0);
+    if (AUX == 0) {  // Eq. (16): phi u_b d_b u_a, central differences of u
+        M phi = g[0];
+#pragma unroll
+        for (int i = 1; i < Q; ++i) phi += g[i];
+        M dd[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const M dxc = ld_at(u + c * pitch, uat(1, 0, 0)) - ld_at(u + c * pitch, uat(-1, 0, 0));
+            const M dyc = ld_at(u + c * pitch, uat(0, 1, 0)) - ld_at(u + c * pitch, uat(0, -1, 0));
+            const M dzc = ld_at(u + c * pitch, uat(0, 0, 1)) - ld_at(u + c * pitch, uat(0, 0, -1));
+            dd[c] = M(0.5) * (ux * dxc + uy * dyc + uz * dzc);
+        }
+        Ax = phi * dd[0];
+        Ay = phi * dd[1];
+        Az = phi * dd[2];
+    }
+    Relax<M> rr;
+    rr.w1 = (M)a.w1;
+    rr.w2 = (M)a.w2;
+    rr.beta = (M)a.beta;
+    rr.w3 = M(0);
+    const unsigned fo = (row(0, 0) * (unsigned)pitch + (unsigned)x) * (unsigned)sizeof(M);
+    if (HAS_K) rr = relax_from_k<M>(ld_at(static_cast<const M *>(a.k), fo), (M)a.lambda, M(0));
+    const M s = HAS_S ? ld_at(static_cast<const M *>(a.s), fo) : M(0);
+    M P[Q];
+    collide3<Q, M>(g, ux, uy, uz, rr, Ax, Ay, Az, s, P);
+    if (!live) return;
+#pragma unroll
+    for (int j = 0; j < Q; ++j) st_at(dst + j * pitch, at(0, 0, 0), C::enc(P[j], j, f));
+}
+
 // ---- two steps per launch ---------------------------------------------------------------------------
 //
 // Slot of the LDS exchange of velocity i, which moves along y (others: -1).
@@ -365,7 +449,8 @@ __host__ __device__ constexpr int yslots()
 // the plane's barrier with one block per CU.  Times per step, one / two steps per launch: D3Q19 256^3 FP32
 // 453 / 365 us, FP64 955 / 703, D3Q27 FP32 638 / 550, FP64 1323 / 952; 100 x 100 x 80 D3Q19 FP32 25.9 / 20.1,
 // FP64 60.5 / 38.6, D3Q27 FP32 36.5 / 27.2, FP64 73.2 / 53.2.  FP16 storage is not built: its codec makes the
-// recomputed rows and lanes cost more than the bytes saved (D3Q19 256^3 259 / 291 us).
+// recomputed rows and lanes cost more than the bytes saved (D3Q19 256^3 259 / 291 us), nor is FP64 storage
+// with FP32 math, whose loads in flight spill (D3Q19 90^3 48 / 53 us).
 template <int Q, int MODE, int AUX, bool HAS_K, bool HAS_S, int NW, bool CST>
 __global__ __launch_bounds__(64 * NW) void step3x2_kernel(const StepArgs sa, const int width, const int planes)
 {
@@ -373,7 +458,7 @@ __global__ __launch_bounds__(64 * NW) void step3x2_kernel(const StepArgs sa, con
     using M = typename ModeTraits<MODE>::M;
     using E = typename St::T;
     using C = Codec<St, M>;
-    static_assert(!is_f16_mode(MODE), "a step-1 value passes its codec unchanged");
+    static_assert(MODE == MODE_F64_F64 || MODE == MODE_F32_F32, "a step-1 value passes its codec unchanged");
     constexpr int NS = yslots<Q>();
     __shared__ M xch[2 * NS * NW * 64 + 2];  // one spare element at either end (lanes without a neighbour)
     const InstDesc &a = sa.d;
@@ -693,6 +778,23 @@ hipError_t launch_step3_st(const StepArgs &a, hipStream_t st)
                          : launch_step3_rows<Q, MODE, AUX, ROWS, false>(a, st);
 }
 
+template <int Q, int MODE, int AUX>
+hipError_t launch_step3_flat(const StepArgs &a, hipStream_t st)
+{
+    const int64_t nodes = (int64_t)a.d.L.nx * rows_of(a.d.L);
+    if (a.d.L.nx < 32 || pop_elems(a.d.L) * (int64_t)sizeof(typename ModeTraits<MODE>::St::T) > (int64_t)UINT32_MAX ||
+        vel_elems(a.d.L) * (int64_t)sizeof(typename ModeTraits<MODE>::M) > (int64_t)UINT32_MAX)
+        return hipErrorInvalidValue;
+    const int nb = (int)((nodes + 255) / 256);
+    const size_t lds = (size_t)a.d.lc.lds_reserve;  // unused LDS that caps the resident waves
+    const bool hk = a.d.has_k, hs = a.d.has_s;
+    if (hk && hs) step3_flat_kernel<Q, MODE, AUX, true, true><<<nb, 256, lds, st>>>(a);
+    else if (hk) step3_flat_kernel<Q, MODE, AUX, true, false><<<nb, 256, lds, st>>>(a);
+    else if (hs) step3_flat_kernel<Q, MODE, AUX, false, true><<<nb, 256, lds, st>>>(a);
+    else step3_flat_kernel<Q, MODE, AUX, false, false><<<nb, 256, lds, st>>>(a);
+    return hipGetLastError();
+}
+
 // One buffer in place (stores 2; one row per wave): the one-row instantiation, whose Q loads and
 // stores keep the scalar-base + 32-bit-offset form (the walking loop's 64-bit addresses would keep
 // up to 27 store addresses in vector registers).
@@ -707,6 +809,7 @@ hipError_t launch_step3_aux(const StepArgs &a, hipStream_t st)
         }
         return hipErrorInvalidValue;
     }
+    if (a.d.lc.flat) return launch_step3_flat<Q, MODE, AUX>(a, st);
     if constexpr (MODE == MODE_F16S_F32) {
         if (a.d.lc.rows == 1) return launch_step3_st<Q, MODE, AUX, 1>(a, st);
     }
@@ -751,7 +854,6 @@ hipError_t launch_step3x2(int mode, int aux, const StepArgs &a, const StripLaunc
     const bool q27 = a.d.L.q == 27;
     switch (mode) {
     case MODE_F64_F64: return q27 ? launch_step3x2_mode<27, MODE_F64_F64>(aux, a, s, st) : launch_step3x2_mode<19, MODE_F64_F64>(aux, a, s, st);
-    case MODE_F64_F32: return q27 ? launch_step3x2_mode<27, MODE_F64_F32>(aux, a, s, st) : launch_step3x2_mode<19, MODE_F64_F32>(aux, a, s, st);
     case MODE_F32_F32: return q27 ? launch_step3x2_mode<27, MODE_F32_F32>(aux, a, s, st) : launch_step3x2_mode<19, MODE_F32_F32>(aux, a, s, st);
     default: return hipErrorInvalidValue;
     }
