@@ -700,16 +700,57 @@ StripLaunch planes_default(const lbm_ctx *c)
     const double two = 1.0 + (double)least * (f64 ? (L.q == 27 ? 5.7 : 4.2) : (L.q == 27 ? 6.0 : 6.2)) / 2.0;
     const double one = one_buffer_3d(c) ? 2.0 + (double)lines_touched(in, 1) * 2.0 / 6.5e6 : 2.0 + (double)L.nx * L.ny * L.nz * (2.0 * L.q * store_bytes(in.mode) + 3.0 * math_bytes(in.mode)) / 5.6e6;
     if (two > 0.95 * one) return StripLaunch{};
+    s.steps = 2;
     s.cached = in.lc.stores == 1 || (s.cols * store_bytes(in.mode)) % 64 != 0;
     return s;
 }
 
+// Patches of a small lattice (periodic or between walls, local or no aux term), or patch 0.  A patch of W waves
+// writes W - 2 (T - 1) rows of 64 - 2 T columns, so the deepest (8 steps, 16 waves) recomputes the most and the
+// 4-step ones of 12 and 16 waves fewer rows; the first of them whose blocks all run at once (one per CU) is
+// taken.  Us per step with (8,16) / (4,12) / (4,16) / strips: FP32 128^2 0.99 / 1.27 / 1.41 / 1.80, 160^2 (320
+// blocks of the first) 1.32 / 1.28 / 1.42 / 1.82, 256^2 1.74 / 1.33 / 1.48 / 2.11, 320^2 2.53 / 1.73 / 1.53 /
+// 2.20; FP64 128^2 1.26 / 1.55 / 1.80 / 2.01, 160^2 2.16 / 1.57 / 1.81 / 2.05, 320^2 4.62 / 2.23 / 1.98 / 2.59.
+// Beyond, FP64 (one block of 16 waves per CU by its LDS, two of 12) takes 12 waves up to 512^2 (480^2 3.41
+// against strips 3.90, 512^2 4.17 / 4.35, 600^2 4.96 / 4.84); the others 12 while two blocks per CU hold the
+// lattice (384^2 FP32 1.76, 16 waves 2.04, strips 2.42), then 16 (512^2 2.90 / strips 3.70, 1000^2 6.26 / 7.15,
+// 1120^2 7.30 / 8.02; 1200^2 8.46 / 8.84 and 1448^2 10.8 / 9.65 stay on strips).  FP16 with stochastic rounding,
+// which has two-step tiles instead of strips there, to 1514^2 (1448^2 17.2 / 18.6; 2048^2 33 / 26).
+StripLaunch patch_default(const Instance &in)
+{
+    StripLaunch s;
+    const auto blocks = [&](int T, int W) {
+        const int V = strip_width(T, 1), H = W - 2 * (T - 1);
+        return (int64_t)((in.p.nx + V - 1) / V) * ((in.p.ny + H - 1) / H);
+    };
+    const auto take = [&](int T, int W) {
+        s.rows = s.cols = 1;
+        s.steps = T;
+        s.patch = W;
+        return s;
+    };
+    if (blocks(8, 16) <= 256) return take(8, 16);
+    if (blocks(4, 12) <= 256) return take(4, 12);
+    if (blocks(4, 16) <= 256) return take(4, 16);
+    if (in.mode == MODE_F64_F64) return blocks(4, 12) <= 896 ? take(4, 12) : s;
+    if (blocks(4, 12) <= 512) return take(4, 12);
+    return blocks(4, 16) <= (in.mode == MODE_F16SR_F32 ? 4096 : 2400) ? take(4, 16) : s;
+}
+
+// Launch for the steps that a multiple of s.steps leaves over: eight-step patches have four-step ones.
+StripLaunch rest_of(StripLaunch s)
+{
+    s.patch = s.steps == 8 ? 12 : 0;
+    s.steps = s.steps == 8 ? 4 : 0;
+    return s;
+}
+
 // The strip launch of a context in its default launch shape, or rows 0.  `touched`: bytes its steps touch.
-// One D2Q9 TRT-R instance in two buffers, periodic or between walls, of at least 16 rows (a shorter lattice
-// would recompute more than it saves), or a uniform batch of such (periodic, FP64 or FP32 storage).
+// One D2Q9 TRT-R instance in two buffers, periodic or between walls: patches while it is small, else strips if
+// it has at least 16 rows (a shorter lattice would recompute more than it saves); or a uniform batch of such (periodic, FP64 or FP32 storage).
 // Measured in MLUPS, without strips / with: local aux term FP32 2048^2 131k / 206k, 8192^2 140k / 223k,
-// 256^2 24k / 31k, FP64 8192^2 69k / 126k; flux form FP32 2048^2 92k / 164k, 512^2 32k / 47k, FP64 4096^2
-// 57k / 83k; walls FP32 1000 x 500 63k / 104k, FP64 300 x 100 6k / 11k; 128 instances of 32^2 .. 512^2 FP32
+// FP64 8192^2 69k / 126k; flux form FP32 2048^2 92k / 164k, 512^2 32k / 47k, FP64 4096^2
+// 57k / 83k; walls FP32 1000 x 500 63k / 104k (patches 118k); 128 instances of 32^2 .. 512^2 FP32
 // 105k / 178k.
 // Columns per lane: two for FP16 from 12e6 nodes on (even nx, local or no aux term), 48 rows (8192^2 with D
 // 180k / 210k, one column 196k; 4096^2 166k / 194k, one column 171k).  FP16 states of narrow lattices that
@@ -732,13 +773,19 @@ StripLaunch strip_default(const lbm_ctx *c, size_t touched, bool batch_fuses)
         for (const Instance &i : c->inst)
             if (i.p.ny < 16) return s;
         s.rows = kBatchStripRows;
+        s.steps = kStripSteps;
         return s;
     }
     if (is3d(in)) return planes_default(c);
     const int64_t nodes = (int64_t)in.p.nx * in.p.ny;
     if (in.p.lattice != LBM_LATTICE_D2Q9 || in.p.boundary == LBM_BC_NEE || (in.p.tau3 != 0.0 && in.p.tau3 != 1.0) ||
-        in.p.ny < 16 || in.lc.stores == 2)
+        in.lc.stores == 2)
         return s;
+    if (in.p.aux != LBM_AUX_FLUX) {
+        s = patch_default(in);
+        if (s.patch > 0) return s;
+    }
+    if (in.p.ny < 16) return s;
     const bool walls = in.p.boundary == LBM_BC_WALLS, flux = in.p.aux == LBM_AUX_FLUX;
     const bool pairs = f16 && !walls && !flux && in.p.nx % 2 == 0 && nodes >= 12000000;
     if (in.mode == MODE_F16SR_F32 && !pairs) return s;
@@ -747,6 +794,7 @@ StripLaunch strip_default(const lbm_ctx *c, size_t touched, bool batch_fuses)
         return s;
     s.rows = pairs ? 48 : strip_rows(in.mode, in.p.nx, in.p.ny, flux);
     s.cols = pairs ? 2 : 1;
+    s.steps = flux ? kFluxStripSteps : kStripSteps;
     if (in.mode == MODE_F32_F32 && !flux && !walls) s.lds_reserve = lds_reserve_for(nodes >= 7000000 ? 2 : 3, c->lds_per_cu);
     s.cached = in.lc.stores == 1 || (store_bytes(in.mode) < 8 && !flux && touched > 2 * kInfinityCacheBytes);
     return s;
@@ -845,14 +893,8 @@ int enqueue_fused(lbm_ctx *c, hipStream_t st)
     return LBM_OK;
 }
 
-// Steps of one strip launch.
-int strip_steps(const lbm_ctx *c)
-{
-    return is3d(c->inst[0]) ? 2 : (c->inst[0].p.aux == LBM_AUX_FLUX ? kFluxStripSteps : kStripSteps);
-}
-
-// Enqueues strip_steps steps of every instance.
-int enqueue_strips(lbm_ctx *c, hipStream_t st)
+// Enqueues how.steps steps of every instance.
+int enqueue_strips(lbm_ctx *c, const StripLaunch &how, hipStream_t st)
 {
     if (c->inst.size() > 1) {
         BatchArgs b;
@@ -861,7 +903,7 @@ int enqueue_strips(lbm_ctx *c, hipStream_t st)
         b.block_start = nullptr;
         b.parity = c->parity;
         b.one_row = 0;
-        hipError_t e = launch_batched_strips(c->inst[0].mode, c->inst[0].p.aux, b, c->strips.rows, c->sched[2].nblocks, st);
+        hipError_t e = launch_batched_strips(c->inst[0].mode, c->inst[0].p.aux, b, how.rows, c->sched[2].nblocks, st);
         if (e != hipSuccess) return hip_fail(e, "batched strip kernel launch");
         c->parity ^= 1;
         return LBM_OK;
@@ -869,8 +911,8 @@ int enqueue_strips(lbm_ctx *c, hipStream_t st)
     StepArgs a;
     a.d = c->h_desc[0];
     a.parity = c->parity;
-    hipError_t e = is3d(c->inst[0]) ? launch_step3x2(c->inst[0].mode, c->inst[0].p.aux, a, c->strips, st)
-                                    : launch_strips(c->inst[0].mode, c->inst[0].p.aux, a, c->strips, st);
+    const auto launch = is3d(c->inst[0]) ? launch_step3x2 : how.patch > 0 ? launch_patches : launch_strips;
+    hipError_t e = launch(c->inst[0].mode, c->inst[0].p.aux, a, how, st);
     if (e != hipSuccess) return hip_fail(e, "strip kernel launch");
     c->parity ^= 1;
     return LBM_OK;
@@ -892,7 +934,7 @@ int graph_for(lbm_ctx *c, hipGraphExec_t *out)
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     int rc = LBM_OK;
     if (c->strips_on)
-        for (int t = 0; t < kGraphSteps / strip_steps(c) && rc == LBM_OK; ++t) rc = enqueue_strips(c, c->capture);
+        for (int t = 0; t < kGraphSteps / c->strips.steps && rc == LBM_OK; ++t) rc = enqueue_strips(c, c->strips, c->capture);
     else if (fused(c))
         for (int t = 0; t < kGraphSteps / 2 && rc == LBM_OK; ++t) rc = enqueue_fused(c, c->capture);
     else
@@ -1227,10 +1269,11 @@ int lbm_step(lbm_ctx *c, int32_t nsteps, const double *const *ux, const double *
         }
     }
     if (c->strips_on)
-        for (; left >= strip_steps(c); left -= strip_steps(c)) {
-            rc = enqueue_strips(c, c->stream);
-            if (rc) return account(rc);
-        }
+        for (const StripLaunch &how : {c->strips, rest_of(c->strips)})
+            for (; how.steps > 0 && left >= how.steps; left -= how.steps) {
+                rc = enqueue_strips(c, how, c->stream);
+                if (rc) return account(rc);
+            }
     if (fused(c))
         for (; left >= 2; left -= 2) {
             rc = enqueue_fused(c, c->stream);

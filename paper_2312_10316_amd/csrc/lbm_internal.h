@@ -199,6 +199,9 @@ hipError_t launch_step(int mode, int aux, const StepArgs &a, hipStream_t st);
 // Two steps per launch (lbm_fused.hip): D2Q9, periodic, aux LOCAL or NONE, two buffers (reads
 // buf[parity], writes buf[parity ^ 1] two steps later).  lcf.fuse_width columns x lcf.rows rows per tile.
 hipError_t launch_step2(int mode, int aux, const StepArgs &a, hipStream_t st);
+// The same for many instances in one launch: block b runs work items (instance, fused tile) as the
+// one-step batched kernel does; every instance has tiles of `width` columns (128, 256 or 512).
+hipError_t launch_batched_step2(int mode, int aux, const BatchArgs &a, int nblocks, int width, hipStream_t st);
 // kStripSteps steps per launch on strips of `rows` rows and `cols` columns per lane that one wave owns
 // (lbm_strips.h): D2Q9 TRT-R, two buffers, periodic (any aux term; the flux form kFluxStripSteps steps, not
 // with stochastic rounding) or between walls (aux LOCAL or NONE; not FP64 storage with FP32 math, not
@@ -212,14 +215,16 @@ struct StripLaunch {
     int cols = 1;
     bool cached = false;  // stores: as Launch::stores 1, else 0
     int lds_reserve = 0;  // dynamic LDS bytes reserved per block to cap the resident waves (0: no cap)
+    int steps = 0;        // steps per launch
+    int patch = 0;        // waves of a patch (small lattices: one row per wave instead of strips), or 0
 };
 hipError_t launch_strips(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
+// s.steps steps per launch on patches of s.patch waves (lbm_patches.h): 8 steps with 16 waves, 4 with 12 or 16.
+// D2Q9 TRT-R, two buffers, periodic or between walls, aux LOCAL or NONE, cached stores.
+hipError_t launch_patches(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
 // kStripSteps steps of many periodic instances in one launch (aux LOCAL or NONE, FP64 or FP32 storage): work
 // item i is strip `tile` (of `rows` rows) of instance `inst`; cached stores.
 hipError_t launch_batched_strips(int mode, int aux, const BatchArgs &a, int rows, int items, hipStream_t st);
-// The same for many instances in one launch: block b runs work items (instance, fused tile) as the
-// one-step batched kernel does; every instance has tiles of `width` columns (128, 256 or 512).
-hipError_t launch_batched_step2(int mode, int aux, const BatchArgs &a, int nblocks, int width, hipStream_t st);
 hipError_t launch_batched_step(int mode, int aux, const BatchArgs &a, int nblocks, int lds_reserve, hipStream_t st);
 hipError_t launch_init(int mode, const InitArgs &a, hipStream_t st);
 // F16SR: sets *slot = level (one lane of one block; kept out of graph captures by the callers).

@@ -25,6 +25,7 @@
 
 #include "lbm_internal.h"
 #include "lbm_kernel_common.h"
+#include "lbm_patches.h"
 
 namespace lbm {
 namespace {
