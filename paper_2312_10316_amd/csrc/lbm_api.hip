@@ -342,6 +342,7 @@ struct Instance {
     char *alt;   // the workspace's second population buffer (buf[1] unless the instance runs in place)
     void *u, *k, *s, *bc;
     lbm_launch shape;  // the default launch shape as reported
+    bool shape_on;     // it is set
     bool flat_ok;      // single steps of that shape run on the gapless 3D kernel
     bool one_ok;       // that shape (two buffers) runs on one buffer in place
     bool one_on;       // it is set, and does
@@ -617,6 +618,7 @@ void update_strips(lbm_ctx *c)
         lbm_launch now = {};
         lbm_get_launch(c, k, &now);
         const bool same = std::memcmp(&now, &in.shape, sizeof now) == 0;
+        in.shape_on = same;
         c->strips_on = c->strips_on && same;
         in.lc.flat = in.lc1.flat = same && in.flat_ok ? 1 : 0;
     }
@@ -1651,12 +1653,25 @@ int lbm_adjoint_segment(lbm_ctx *c, int32_t inst, void *states, int32_t nsteps, 
     // Recomputation: image j + 1 = one step of image j, image to image with two buffers whatever the
     // context's own store kind (state images are always in the two-buffer layout).  The next launch
     // reads each new image at once, so a context whose steps stream only because they fit the L2 caches
-    // recomputes with cached stores (512^2 FP32: 5.3 us per step against 6.2 us streaming).
+    // recomputes with cached stores (512^2 FP32, single steps: 5.3 us against 6.2 us streaming).
     StepArgs a;
     a.d = c->h_desc[inst];
     if (a.d.lc.stores == 2 || c->l2_streams) a.d.lc.stores = 1;  // its lc is the one-step launch
     a.parity = 0;
-    for (int32_t j = 0; j + 1 < nsteps; ++j) {
+    // In the default launch shape four steps at a time run on patches, every image stored: of 12 waves below 3e5
+    // nodes, else of 16.  So does the reverse sweep in any shape; FP64 states with FP32 lam keep 12 waves.  Us per
+    // segment of 9 steps, single steps / images on 12 / on 16 waves: FP32 512^2 102 / 92 / 94, 1000^2 371 / 339 / 330,
+    // 2500^2 2236 / 2258 / 2221; FP64 384^2 122 / 96 / 106, 1000^2 689 / 625 / 609; and the reverse sweep on 12 / on
+    // 16: FP32 384^2 63 / 69 (single 76), 1000^2 289 / 283; FP64 storage with FP32 math 2048^2 1718 / 1755 (2098).
+    const int waves = (int64_t)in.p.nx * in.p.ny < 300000 ? 12 : 16, adj_waves = in.mode == MODE_F64_F32 ? 12 : waves;
+    int32_t j = 0;
+    for (; in.shape_on && j + kPatchImages < nsteps; j += kPatchImages) {
+        a.d.buf[0] = img + (size_t)j * sb;
+        a.d.buf[1] = img + (size_t)(j + 1) * sb;
+        hipError_t e = launch_patch_images(in.mode, in.p.aux, a, waves, (int64_t)sb, c->stream);
+        if (e != hipSuccess) return hip_fail(e, "patch kernel launch (adjoint segment)");
+    }
+    for (; j + 1 < nsteps; ++j) {
         a.d.buf[0] = img + (size_t)j * sb;
         a.d.buf[1] = img + (size_t)(j + 1) * sb;
         hipError_t e = launch_step(in.mode, in.p.aux, a, c->stream);
@@ -1665,7 +1680,16 @@ int lbm_adjoint_segment(lbm_ctx *c, int32_t inst, void *states, int32_t nsteps, 
     // Reverse sweep: dL/dg^{j} from dL/dg^{j+1}, j = nsteps - 1 .. 0, alternating the two arrays.
     AdjArgs g = adj_args(in, dLdD);
     void *cur = lam, *nxt = lam_tmp;
-    for (int32_t j = nsteps - 1; j >= 0; --j) {
+    j = nsteps - 1;
+    for (; j + 1 >= kAdjointPatchSteps; j -= kAdjointPatchSteps) {
+        g.state = img + (size_t)j * sb;
+        g.lam_in = cur;
+        g.lam_out = nxt;
+        hipError_t e = launch_adjoint_patches(in.mode, in.p.aux, g, adj_waves, (int64_t)sb, c->stream);
+        if (e != hipSuccess) return hip_fail(e, "adjoint kernel launch (adjoint segment)");
+        std::swap(cur, nxt);
+    }
+    for (; j >= 0; --j) {
         g.state = img + (size_t)j * sb;
         g.lam_in = cur;
         g.lam_out = nxt;

@@ -222,6 +222,10 @@ hipError_t launch_strips(int mode, int aux, const StepArgs &a, const StripLaunch
 // s.steps steps per launch on patches of s.patch waves (lbm_patches.h): 8 steps with 16 waves, 4 with 12 or 16.
 // D2Q9 TRT-R, two buffers, periodic or between walls, aux LOCAL or NONE, cached stores.
 hipError_t launch_patches(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
+// The same with every step's state stored, image_bytes apart from buf[parity ^ 1] on: kPatchImages steps, 12 or
+// 16 waves, periodic, FP64 or FP32 storage.
+constexpr int kPatchImages = 4;
+hipError_t launch_patch_images(int mode, int aux, const StepArgs &a, int waves, int64_t image_bytes, hipStream_t st);
 // kStripSteps steps of many periodic instances in one launch (aux LOCAL or NONE, FP64 or FP32 storage): work
 // item i is strip `tile` (of `rows` rows) of instance `inst`; cached stores.
 hipError_t launch_batched_strips(int mode, int aux, const BatchArgs &a, int rows, int items, hipStream_t st);
@@ -237,6 +241,10 @@ hipError_t launch_populations(int mode, const PopArgs &a, hipStream_t st);
 // (either way: the map is its own inverse); src and dst must differ.
 hipError_t launch_relayout(size_t elem_bytes, const void *src, void *dst, const Layout &L, hipStream_t st);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, bool cached, hipStream_t st);
+// kAdjointPatchSteps adjoint steps on patches of `waves` waves (12 or 16): a.state is the last step's image, the
+// earlier ones lie image_bytes apart below it.
+constexpr int kAdjointPatchSteps = 4;
+hipError_t launch_adjoint_patches(int mode, int aux, const AdjArgs &a, int waves, int64_t image_bytes, hipStream_t st);
 hipError_t launch_adjoint(int mode, int aux, const AdjArgs &a, hipStream_t st);
 // D3Q19 and D3Q27 (lbm_kernels3d.hip, chosen by L.q): storage modes F64_F64, F64_F32, F32_F32; aux
 // LOCAL or NONE; periodic.

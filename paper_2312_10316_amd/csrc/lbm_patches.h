@@ -24,8 +24,9 @@ namespace {
 // latency of a node update and the exchange.  Us per step, strips / patches: FP64 64^2 1.96 / 1.17, FP32 128^2
 // 1.80 / 0.99, 256^2 2.11 / 1.33, 512^2 3.73 / 2.90, FP16 with stochastic rounding 300^2 3.96 / 2.14.
 // Bitwise T single steps, as the strips.
-template <int MODE, int AUX, bool HAS_K, bool HAS_S, int T, int NW, int BC>
-__global__ __launch_bounds__(64 * NW) void patch_kernel(const StepArgs sa)
+// IMG: every step's state is stored, image_bytes apart from buf[parity ^ 1] on (the adjoint's recomputation).
+template <int MODE, int AUX, bool HAS_K, bool HAS_S, int T, int NW, int BC, bool IMG = false>
+__global__ __launch_bounds__(64 * NW) void patch_kernel(const StepArgs sa, const int64_t image_bytes)
 {
     using St = typename ModeTraits<MODE>::St;
     using M = typename ModeTraits<MODE>::M;
@@ -117,13 +118,14 @@ __global__ __launch_bounds__(64 * NW) void patch_kernel(const StepArgs sa)
             }
             collide<M, false>(g, ux, uy, r, Ax, Ay, s, P);
             const auto rb = C::bits(f, level + n, (int64_t)y * nx, (unsigned)xi);
-            if (n == T) {
+            if (IMG || n == T) {
                 if (live && out) {
-                    E *__restrict__ o = static_cast<E *>(d.buf[sa.parity ^ 1]) + (int64_t)y * 9 * pitch;
+                    E *__restrict__ o = reinterpret_cast<E *>(static_cast<char *>(d.buf[sa.parity ^ 1]) + (IMG ? n - 1 : 0) * image_bytes) + (int64_t)y * 9 * pitch;
 #pragma unroll
                     for (int i = 0; i < 9; ++i) st_at(o + i * pitch, bc, C::enc(P[i], i, f, rb));
                 }
-            } else {
+            }
+            if (n < T) {
                 X c[9];
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
@@ -160,17 +162,17 @@ __global__ __launch_bounds__(64 * NW) void patch_kernel(const StepArgs sa)
     }
 }
 
-template <int MODE, int AUX, int T, int NW, int BC>
-hipError_t launch_patches_st(const StepArgs &a, hipStream_t st)
+template <int MODE, int AUX, int T, int NW, int BC, bool IMG = false>
+hipError_t launch_patches_st(const StepArgs &a, hipStream_t st, int64_t image_bytes = 0)
 {
     constexpr int V = strip_width(T, 1), H = NW - 2 * (T - 1);
     const int64_t nb = (int64_t)((a.d.L.nx + V - 1) / V) * ((a.d.L.ny + H - 1) / H);
     if (nb > INT32_MAX / 16) return hipErrorInvalidValue;
     const bool hk = a.d.has_k, hs = a.d.has_s;
-    if (hk && hs) patch_kernel<MODE, AUX, true, true, T, NW, BC><<<(int)nb, 64 * NW, 0, st>>>(a);
-    else if (hk) patch_kernel<MODE, AUX, true, false, T, NW, BC><<<(int)nb, 64 * NW, 0, st>>>(a);
-    else if (hs) patch_kernel<MODE, AUX, false, true, T, NW, BC><<<(int)nb, 64 * NW, 0, st>>>(a);
-    else patch_kernel<MODE, AUX, false, false, T, NW, BC><<<(int)nb, 64 * NW, 0, st>>>(a);
+    if (hk && hs) patch_kernel<MODE, AUX, true, true, T, NW, BC, IMG><<<(int)nb, 64 * NW, 0, st>>>(a, image_bytes);
+    else if (hk) patch_kernel<MODE, AUX, true, false, T, NW, BC, IMG><<<(int)nb, 64 * NW, 0, st>>>(a, image_bytes);
+    else if (hs) patch_kernel<MODE, AUX, false, true, T, NW, BC, IMG><<<(int)nb, 64 * NW, 0, st>>>(a, image_bytes);
+    else patch_kernel<MODE, AUX, false, false, T, NW, BC, IMG><<<(int)nb, 64 * NW, 0, st>>>(a, image_bytes);
     return hipGetLastError();
 }
 
@@ -190,6 +192,14 @@ hipError_t launch_patches_mode(int aux, const StepArgs &a, const StripLaunch &s,
     return aux == 0 ? launch_patches_kind<MODE, 0, 0>(a, s, st) : launch_patches_kind<MODE, 2, 0>(a, s, st);
 }
 
+template <int MODE, int AUX>
+hipError_t launch_patch_images_kind(const StepArgs &a, int waves, int64_t image_bytes, hipStream_t st)
+{
+    if (waves == 12) return launch_patches_st<MODE, AUX, kPatchImages, 12, 0, true>(a, st, image_bytes);
+    if (waves == 16) return launch_patches_st<MODE, AUX, kPatchImages, 16, 0, true>(a, st, image_bytes);
+    return hipErrorInvalidValue;
+}
+
 }  // namespace
 
 hipError_t launch_patches(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st)
@@ -201,6 +211,17 @@ hipError_t launch_patches(int mode, int aux, const StepArgs &a, const StripLaunc
     case MODE_F32_F32: return launch_patches_mode<MODE_F32_F32>(aux, a, s, st);
     case MODE_F16S_F32: return launch_patches_mode<MODE_F16S_F32>(aux, a, s, st);
     case MODE_F16SR_F32: return launch_patches_mode<MODE_F16SR_F32>(aux, a, s, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_patch_images(int mode, int aux, const StepArgs &a, int waves, int64_t image_bytes, hipStream_t st)
+{
+    if (a.d.L.q != 9 || a.d.bckind != 0 || a.d.w3 != 0.0 || aux == 1 || a.d.buf[0] == a.d.buf[1]) return hipErrorInvalidValue;
+    switch (mode) {
+    case MODE_F64_F64: return aux == 0 ? launch_patch_images_kind<MODE_F64_F64, 0>(a, waves, image_bytes, st) : launch_patch_images_kind<MODE_F64_F64, 2>(a, waves, image_bytes, st);
+    case MODE_F64_F32: return aux == 0 ? launch_patch_images_kind<MODE_F64_F32, 0>(a, waves, image_bytes, st) : launch_patch_images_kind<MODE_F64_F32, 2>(a, waves, image_bytes, st);
+    case MODE_F32_F32: return aux == 0 ? launch_patch_images_kind<MODE_F32_F32, 0>(a, waves, image_bytes, st) : launch_patch_images_kind<MODE_F32_F32, 2>(a, waves, image_bytes, st);
     default: return hipErrorInvalidValue;
     }
 }
