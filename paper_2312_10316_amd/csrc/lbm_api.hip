@@ -708,41 +708,54 @@ StripLaunch planes_default(const lbm_ctx *c)
 }
 
 // Patches of a small lattice (periodic or between walls, local or no aux term), or patch 0.  A patch of W waves
-// writes W - 2 (T - 1) rows of 64 - 2 T columns, so the deepest (8 steps, 16 waves) recomputes the most and the
-// 4-step ones of 12 and 16 waves fewer rows; the first of them whose blocks all run at once (one per CU) is
-// taken.  Us per step with (8,16) / (4,12) / (4,16) / strips: FP32 128^2 0.99 / 1.27 / 1.41 / 1.80, 160^2 (320
-// blocks of the first) 1.32 / 1.28 / 1.42 / 1.82, 256^2 1.74 / 1.33 / 1.48 / 2.11, 320^2 2.53 / 1.73 / 1.53 /
-// 2.20; FP64 128^2 1.26 / 1.55 / 1.80 / 2.01, 160^2 2.16 / 1.57 / 1.81 / 2.05, 320^2 4.62 / 2.23 / 1.98 / 2.59.
-// Beyond, FP64 (one block of 16 waves per CU by its LDS, two of 12) takes 12 waves up to 512^2 (480^2 3.41
-// against strips 3.90, 512^2 4.17 / 4.35, 600^2 4.96 / 4.84); the others 12 while two blocks per CU hold the
-// lattice (384^2 FP32 1.76, 16 waves 2.04, strips 2.42), then 16 (512^2 2.90 / strips 3.70, 1000^2 6.26 / 7.15,
-// 1120^2 7.30 / 8.02; 1200^2 8.46 / 8.84 and 1448^2 10.8 / 9.65 stay on strips).  FP16 with stochastic rounding,
-// which has two-step tiles instead of strips there, to 1514^2 (1448^2 17.2 / 18.6; 2048^2 33 / 26).
+// of R rows writes W R - 2 (T - 1) rows of 64 - 2 T columns, so the deepest (8 steps, 16 waves) recomputes the most
+// and the others less and less; the first of them whose blocks all run at once (one per CU) is taken.  Us per step
+// with (T, W, R) = (8,16,1) / (4,12,1) / (4,16,1) / strips: FP32 128^2 0.99 / 1.27 / 1.41 / 1.80, 160^2 (320 blocks
+// of the first) 1.32 / 1.28 / 1.42 / 1.82, 256^2 1.74 / 1.33 / 1.48 / 2.11, 320^2 2.53 / 1.73 / 1.53 / 2.20; FP64
+// 128^2 1.26 / 1.55 / 1.80 / 2.01, 160^2 2.16 / 1.57 / 1.81 / 2.05, 320^2 4.62 / 2.23 / 1.98 / 2.59; then (4,16,1) /
+// (4,12,2) / (4,16,2): FP32 448^2 2.17 / 2.05 / 2.41, 512^2 2.99 / 3.20 / 2.62, FP64 448^2 3.41 / 2.90 / 3.45, 512^2
+// 5.15 / 5.22 / 3.81.
+// Beyond, FP64 runs on strips (600^2 best patch 4.79, strips 4.83; 724^2 5.47 / 5.39).  The others compare the
+// rounds of (4,12,2), one block per CU, with the blocks of (4,16,1), two per CU, in us per FP32 launch: 724^2
+// (4,16,1) 3.58 / (4,12,2) 4.07 us per step, 850^2 4.70 / 4.25, 1000^2 6.36 / 5.79 (strips 7.15), 1200^2 8.48 / 7.80
+// (8.9); 1448^2 10.6 / 9.9 stays on strips (9.6).  FP64 storage with FP32 math takes (4,16,1) up to 1120^2 (1000^2
+// 7.96, (4,12,2) 8.13, strips 8.9); FP16 with stochastic rounding, which has two-step tiles instead of strips
+// there, goes on to 1514^2 (1448^2 17.1, two-step tiles 18.6; 2048^2 32 / 26).
+// Between walls, whose reflected populations take registers too, one row per wave is the faster (1000 x 500 FP32
+// (4,16,1) 4.25 us, (4,12,2) 4.73, strips 4.97; periodic FP64 480^2 (4,12,1) 3.41, strips 3.90, 600^2 4.96 / 4.84).
 StripLaunch patch_default(const Instance &in)
 {
     StripLaunch s;
-    const auto blocks = [&](int T, int W) {
-        const int V = strip_width(T, 1), H = W - 2 * (T - 1);
+    const auto blocks = [&](int T, int W, int R) {
+        const int V = strip_width(T, 1), H = W * R - 2 * (T - 1);
         return (int64_t)((in.p.nx + V - 1) / V) * ((in.p.ny + H - 1) / H);
     };
-    const auto take = [&](int T, int W) {
-        s.rows = s.cols = 1;
+    const auto take = [&](int T, int W, int R) {
         s.steps = T;
         s.patch = W;
+        s.rows = R;
+        s.cols = 1;
         return s;
     };
-    if (blocks(8, 16) <= 256) return take(8, 16);
-    if (blocks(4, 12) <= 256) return take(4, 12);
-    if (blocks(4, 16) <= 256) return take(4, 16);
-    if (in.mode == MODE_F64_F64) return blocks(4, 12) <= 896 ? take(4, 12) : s;
-    if (blocks(4, 12) <= 512) return take(4, 12);
-    return blocks(4, 16) <= (in.mode == MODE_F16SR_F32 ? 4096 : 2400) ? take(4, 16) : s;
+    if (blocks(8, 16, 1) <= 256) return take(8, 16, 1);
+    if (blocks(4, 12, 1) <= 256) return take(4, 12, 1);
+    if (blocks(4, 16, 1) <= 256) return take(4, 16, 1);
+    const int64_t b = blocks(4, 16, 1);
+    if (in.p.boundary != LBM_BC_PERIODIC) {
+        if (blocks(4, 12, 1) <= (in.mode == MODE_F64_F64 ? 896 : 512)) return take(4, 12, 1);
+        return in.mode != MODE_F64_F64 && b <= 2400 ? take(4, 16, 1) : s;
+    }
+    if (blocks(4, 12, 2) <= 256) return take(4, 12, 2);
+    if (blocks(4, 16, 2) <= 256) return take(4, 16, 2);
+    if (in.mode == MODE_F64_F64 || b > (in.mode == MODE_F16SR_F32 ? 4096 : in.mode == MODE_F64_F32 ? 2400 : 2800)) return s;
+    const bool rounds = 2.4 + 5.0 * (double)((blocks(4, 12, 2) + 255) / 256) < 3.0 + 0.012 * (double)b;
+    return in.mode != MODE_F64_F32 && rounds ? take(4, 12, 2) : take(4, 16, 1);
 }
 
 // Launch for the steps that a multiple of s.steps leaves over: eight-step patches have four-step ones.
 StripLaunch rest_of(StripLaunch s)
 {
-    s.patch = s.steps == 8 ? 12 : 0;
+    s.patch = s.steps == 8 ? 12 : 0;  // one row per wave, as the eight-step ones
     s.steps = s.steps == 8 ? 4 : 0;
     return s;
 }

@@ -216,10 +216,11 @@ struct StripLaunch {
     bool cached = false;  // stores: as Launch::stores 1, else 0
     int lds_reserve = 0;  // dynamic LDS bytes reserved per block to cap the resident waves (0: no cap)
     int steps = 0;        // steps per launch
-    int patch = 0;        // waves of a patch (small lattices: one row per wave instead of strips), or 0
+    int patch = 0;        // small lattices: waves of a patch of `rows` rows each; 0: strips
 };
 hipError_t launch_strips(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
-// s.steps steps per launch on patches of s.patch waves (lbm_patches.h): 8 steps with 16 waves, 4 with 12 or 16.
+// s.steps steps per launch on patches of s.patch waves (lbm_patches.h) of s.rows rows: 8 steps with 16 waves of one, 4 steps
+// with 12 or 16 waves of one or (periodic) two.
 // D2Q9 TRT-R, two buffers, periodic or between walls, aux LOCAL or NONE, cached stores.
 hipError_t launch_patches(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
 // The same with every step's state stored, image_bytes apart from buf[parity ^ 1] on: kPatchImages steps, 12 or
