@@ -495,11 +495,46 @@ struct lbm_ctx {
     double *partials = nullptr;
     double *result = nullptr;
     int *flag = nullptr;
+    unsigned *macros_done = nullptr;  // finished blocks of a diagnostics launch (device)
+    double *host_result = nullptr;    // this context's slot of pinned host memory, or nullptr: result and a copy
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     int device = -1;                  // the device current at lbm_init (its stream's device)
 };
 
 namespace {
+
+// Slots of 8 doubles in one page of pinned host memory, into which lbm_macros' kernel writes its result (a copy
+// to pageable memory is 10 us of a call).  The page is allocated with the first context and kept; a context
+// holds one slot until lbm_free, and those beyond the 64th do without.
+std::mutex g_slots_mu;
+double *g_slots = nullptr;
+uint64_t g_slots_used = 0;
+
+double *take_result_slot()
+{
+    std::lock_guard<std::mutex> lock(g_slots_mu);
+    if (!g_slots) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, 64 * 8 * sizeof(double), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        g_slots = static_cast<double *>(p);
+    }
+    for (int k = 0; k < 64; ++k)
+        if (!(g_slots_used >> k & 1)) {
+            g_slots_used |= (uint64_t)1 << k;
+            return g_slots + 8 * k;
+        }
+    return nullptr;
+}
+
+void give_result_slot(double *slot)
+{
+    if (!slot) return;
+    std::lock_guard<std::mutex> lock(g_slots_mu);
+    g_slots_used &= ~((uint64_t)1 << ((slot - g_slots) / 8));
+}
 
 bool check_inst(lbm_ctx *c, int32_t inst) { return c && inst >= 0 && inst < (int32_t)c->inst.size(); }
 
@@ -1064,6 +1099,8 @@ int lbm_init(lbm_ctx **out, int32_t n_inst, const lbm_params *p, const lbm_field
     c->partials = reinterpret_cast<double *>(w);
     c->result = reinterpret_cast<double *>(w + kPartialBytes);
     c->flag = reinterpret_cast<int *>(w + kPartialBytes + 256);
+    c->macros_done = reinterpret_cast<unsigned *>(c->flag) + 2;
+    c->host_result = take_result_slot();
     w += align_up(kScratchBytes, kAlign);
     c->inst.resize(n_inst);
     c->uniform = true;
@@ -1304,8 +1341,10 @@ int lbm_step(lbm_ctx *c, int32_t nsteps, const double *const *ux, const double *
 namespace {
 // The diagnostics of lbm_macros with the reduction's per-block partials and result in `partials` and
 // `result` (device).
+// `result` on the host (a pinned slot) is merged by the kernel itself and read after the synchronization; on the
+// device a second launch merges and a copy reads it (the scratch that contexts share has no count of its own).
 int macros_into(lbm_ctx *c, int32_t inst, double *phi_out, const double *ref, lbm_stats *out, double *partials,
-                double *result)
+                double *result, bool on_host)
 {
     Instance &in = c->inst[inst];
     MacroArgs a;
@@ -1318,13 +1357,15 @@ int macros_into(lbm_ctx *c, int32_t inst, double *phi_out, const double *ref, lb
     a.edge.bc = in.bc;
     a.edge.kind = in.lc.stores == 2 && c->parity == 1 ? 3 : in.p.boundary;  // 3: one buffer after a streaming step
     a.partials = partials;
-    hipError_t e = is3d(in) ? launch_macros3(in.mode, a, result, c->stream)
-                            : launch_macros(in.mode, a, result, c->stream);
+    a.result = result;
+    a.done = on_host ? c->macros_done : nullptr;
+    hipError_t e = is3d(in) ? launch_macros3(in.mode, a, c->stream) : launch_macros(in.mode, a, c->stream);
     if (e != hipSuccess) return hip_fail(e, "macros kernel launch");
     double r[6];
-    e = hipMemcpyAsync(r, result, sizeof r, hipMemcpyDeviceToHost, c->stream);
+    if (!on_host) e = hipMemcpyAsync(r, result, sizeof r, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(e, "lbm_macros: reading the result");
+    if (on_host) std::memcpy(r, result, sizeof r);
     const double nn = (double)in.L.nx * in.L.ny * in.L.nz;
     out->mass = r[0];
     out->rms_err = ref ? std::sqrt(r[1] / nn) : 0.0;
@@ -1344,7 +1385,7 @@ int lbm_macros(lbm_ctx *c, int32_t inst, double *phi_out, const double *ref, lbm
     g_err[0] = 0;
     if (!check_inst(c, inst)) return fail(LBM_E_STATE, "lbm_macros: bad context or instance %d", inst);
     if (!out) return fail(LBM_E_ARG, "lbm_macros: out is NULL");
-    return macros_into(c, inst, phi_out, ref, out, c->partials, c->result);
+    return macros_into(c, inst, phi_out, ref, out, c->partials, c->host_result ? c->host_result : c->result, c->host_result != nullptr);
 }
 
 int lbm_macros_static(lbm_ctx *c, int32_t inst, double *phi_out, const double *ref, lbm_stats *out)
@@ -1362,7 +1403,7 @@ int lbm_macros_static(lbm_ctx *c, int32_t inst, double *phi_out, const double *r
     if ((size_t)blocks * kMacroPartialDoubles + 8 > kStaticScratchDoubles)
         return fail(LBM_E_ARG, "lbm_macros_static: %lld reduction blocks exceed the static scratch of %zu bytes",
                     (long long)blocks, kStaticScratchDoubles * sizeof(double));
-    return macros_into(c, inst, phi_out, ref, out, sp, sp + (size_t)kMacroBlocks * kMacroPartialDoubles);
+    return macros_into(c, inst, phi_out, ref, out, sp, sp + (size_t)kMacroBlocks * kMacroPartialDoubles, false);
 }
 
 int lbm_set_velocity(lbm_ctx *c, int32_t inst, const double *ux, const double *uy, const double *uz)
@@ -1780,6 +1821,7 @@ int lbm_free(lbm_ctx *c)
     if (e != hipSuccess) rc = hip_fail(e, "lbm_free: synchronizing");
     drop_graphs(c);
     if (c->capture) (void)hipStreamDestroy(c->capture);
+    give_result_slot(c->host_result);
     if (c->owns_ws && c->ws) {
         e = hipFree(c->ws);
         if (e != hipSuccess && rc == LBM_OK) rc = hip_fail(e, "lbm_free: hipFree");

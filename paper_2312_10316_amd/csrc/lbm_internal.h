@@ -166,6 +166,8 @@ struct MacroArgs {
     F16Params f16;
     EdgeArgs edge;
     double *partials;  // per block: kMacroPartialDoubles
+    double *result;    // 6 doubles, device or mapped host memory
+    unsigned *done;    // count of finished blocks (0 between launches): the last block merges; nullptr: a second launch does
 };
 
 constexpr int kMacroPartialDoubles = 10;  // mass(s,c) err2(s,c) ref2(s,c) maxerr maxphi nonfinite pad
@@ -235,8 +237,8 @@ hipError_t launch_init(int mode, const InitArgs &a, hipStream_t st);
 // F16SR: sets *slot = level (one lane of one block; kept out of graph captures by the callers).
 hipError_t launch_set_clock(int64_t *slot, int64_t level, hipStream_t st);
 hipError_t launch_prep(int mode, const PrepArgs &a, hipStream_t st);
-hipError_t launch_macros(int mode, const MacroArgs &a, double *result, hipStream_t st);
-hipError_t launch_macros_finalize(const double *partials, int nblocks, double *result, hipStream_t st);
+hipError_t launch_macros(int mode, const MacroArgs &a, hipStream_t st);
+hipError_t launch_macros_finalize(const MacroArgs &a, int nblocks, hipStream_t st);
 hipError_t launch_populations(int mode, const PopArgs &a, hipStream_t st);
 // D2Q9 state images between the standard layout and the one-buffer layout after a streaming step
 // (either way: the map is its own inverse); src and dst must differ.
@@ -256,7 +258,7 @@ hipError_t launch_step3(int mode, int aux, const StepArgs &a, hipStream_t st);
 constexpr int step3x2_waves(int q, int mode) { return mode == MODE_F64_F64 ? 6 : (q == 27 ? 12 : 16); }
 hipError_t launch_step3x2(int mode, int aux, const StepArgs &a, const StripLaunch &s, hipStream_t st);
 hipError_t launch_init3(int mode, const InitArgs &a, hipStream_t st);
-hipError_t launch_macros3(int mode, const MacroArgs &a, double *result, hipStream_t st);
+hipError_t launch_macros3(int mode, const MacroArgs &a, hipStream_t st);
 hipError_t launch_populations3(int mode, const PopArgs &a, hipStream_t st);
 hipError_t launch_relayout3(size_t elem_bytes, const void *src, void *dst, const Layout &L, hipStream_t st);
 hipError_t launch_adjoint_seed(int mode, const double *dphi, void *lam, const Layout &L, hipStream_t st);

@@ -215,6 +215,57 @@ __device__ inline void block_reduce(CSum (&cs)[3], double &mx0, double &mx1, dou
     }
 }
 
+// One block: merges the partials of nblocks blocks; result[0..2] = mass, sum err^2, sum ref^2 (s + c),
+// result[3] = max err, result[4] = max |phi|, result[5] = non-finite count.
+__device__ inline void macros_merge(const double *partials, int nblocks, double *result)
+{
+    CSum cs[3] = {{0, 0}, {0, 0}, {0, 0}};
+    double mx0 = 0, mx1 = 0, cnt = 0;
+    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+        const double *p = partials + (int64_t)b * kMacroPartialDoubles;
+        for (int k = 0; k < 3; ++k) cs[k] = csum_merge(cs[k], CSum{p[2 * k], p[2 * k + 1]});
+        mx0 = fmax(mx0, p[6]);
+        mx1 = fmax(mx1, p[7]);
+        cnt += p[8];
+    }
+    block_reduce(cs, mx0, mx1, cnt);
+    if (threadIdx.x == 0) {
+        for (int k = 0; k < 3; ++k) result[k] = cs[k].s + cs[k].c;
+        result[3] = mx0;
+        result[4] = mx1;
+        result[5] = cnt;
+    }
+}
+
+// End of a diagnostics kernel: the block's partials, and with a.done the merge by the last block to finish (a
+// second launch is 4 us of a call on a small lattice).  The fences order the partials before the count and
+// the merge after it, across the XCDs' L2 caches; the last block leaves the count at 0 for the next launch.
+__device__ inline void macros_end(const MacroArgs &a, CSum (&cs)[3], double maxerr, double maxphi, double nonfinite)
+{
+    block_reduce(cs, maxerr, maxphi, nonfinite);
+    __shared__ bool last;
+    if (threadIdx.x == 0) {
+        double *p = a.partials + (int64_t)blockIdx.x * kMacroPartialDoubles;
+        for (int k = 0; k < 3; ++k) {
+            p[2 * k] = cs[k].s;
+            p[2 * k + 1] = cs[k].c;
+        }
+        p[6] = maxerr;
+        p[7] = maxphi;
+        p[8] = nonfinite;
+        if (a.done) {
+            __threadfence();
+            last = atomicAdd(a.done, 1u) == gridDim.x - 1;
+        }
+    }
+    if (!a.done) return;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    macros_merge(a.partials, (int)gridDim.x, a.result);
+    if (threadIdx.x == 0) *a.done = 0u;
+}
+
 inline int grid_for(int64_t n, int block, int cap)
 {
     int64_t g = (n + block - 1) / block;

@@ -538,12 +538,12 @@ __global__ __launch_bounds__(256) void macros_kernel(const MacroArgs a)
     using M = typename ModeTraits<MODE>::M;
     using T = typename St::T;
     const int nx = a.L.nx, ny = a.L.ny;
-    const int64_t N = (int64_t)nx * ny;
+    const unsigned N = (unsigned)nx * (unsigned)ny;  // at most 2^31; 64-bit divisions are 1.5 us of a small lattice's call
     const T *src = static_cast<const T *>(a.src);
     CSum cs[3] = {{0, 0}, {0, 0}, {0, 0}};  // mass, sum err^2, sum ref^2
     double maxerr = 0, maxphi = 0, nonfinite = 0;
-    for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (int64_t)gridDim.x * blockDim.x) {
-        const int x = (int)(n % nx), y = (int)(n / nx);
+    for (unsigned n = blockIdx.x * blockDim.x + threadIdx.x; n < N; n += gridDim.x * blockDim.x) {
+        const int x = (int)(n % (unsigned)nx), y = (int)(n / (unsigned)nx);
         M g[9];
         state_node<St, M>(src, a.edge, a.L, x, y, a.f16, g);
         double phi = 0;
@@ -563,39 +563,12 @@ __global__ __launch_bounds__(256) void macros_kernel(const MacroArgs a)
             maxerr = fmax(maxerr, fabs(d));
         }
     }
-    block_reduce(cs, maxerr, maxphi, nonfinite);
-    if (threadIdx.x == 0) {
-        double *p = a.partials + (int64_t)blockIdx.x * kMacroPartialDoubles;
-        for (int k = 0; k < 3; ++k) {
-            p[2 * k] = cs[k].s;
-            p[2 * k + 1] = cs[k].c;
-        }
-        p[6] = maxerr;
-        p[7] = maxphi;
-        p[8] = nonfinite;
-    }
+    macros_end(a, cs, maxerr, maxphi, nonfinite);
 }
 
-// Single block: merges the per-block partials; result[0..2] = mass, sum err^2, sum ref^2 (s + c),
-// result[3] = max err, result[4] = max |phi|, result[5] = non-finite count.
 __global__ __launch_bounds__(256) void macros_finalize(const double *partials, int nblocks, double *result)
 {
-    CSum cs[3] = {{0, 0}, {0, 0}, {0, 0}};
-    double mx0 = 0, mx1 = 0, cnt = 0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-        const double *p = partials + (int64_t)b * kMacroPartialDoubles;
-        for (int k = 0; k < 3; ++k) cs[k] = csum_merge(cs[k], CSum{p[2 * k], p[2 * k + 1]});
-        mx0 = fmax(mx0, p[6]);
-        mx1 = fmax(mx1, p[7]);
-        cnt += p[8];
-    }
-    block_reduce(cs, mx0, mx1, cnt);
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 3; ++k) result[k] = cs[k].s + cs[k].c;
-        result[3] = mx0;
-        result[4] = mx1;
-        result[5] = cnt;
-    }
+    macros_merge(partials, nblocks, result);
 }
 
 template <int MODE>
@@ -817,7 +790,7 @@ hipError_t launch_prep(int mode, const PrepArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_macros(int mode, const MacroArgs &a, double *result, hipStream_t st)
+hipError_t launch_macros(int mode, const MacroArgs &a, hipStream_t st)
 {
     const int g = grid_for((int64_t)a.L.nx * a.L.ny, 256, kMacroBlocks);
     switch (mode) {
@@ -829,13 +802,13 @@ hipError_t launch_macros(int mode, const MacroArgs &a, double *result, hipStream
     default: return hipErrorInvalidValue;
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_macros_finalize(a.partials, g, result, st);
+    if (e != hipSuccess || a.done) return e;
+    return launch_macros_finalize(a, g, st);
 }
 
-hipError_t launch_macros_finalize(const double *partials, int nblocks, double *result, hipStream_t st)
+hipError_t launch_macros_finalize(const MacroArgs &a, int nblocks, hipStream_t st)
 {
-    macros_finalize<<<1, 256, 0, st>>>(partials, nblocks, result);
+    macros_finalize<<<1, 256, 0, st>>>(a.partials, nblocks, a.result);
     return hipGetLastError();
 }
 

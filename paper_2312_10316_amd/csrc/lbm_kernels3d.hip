@@ -699,15 +699,15 @@ __global__ __launch_bounds__(256) void macros3_kernel(const MacroArgs a)
     using M = typename ModeTraits<MODE>::M;
     using T = typename St::T;
     const int nx = a.L.nx, ny = a.L.ny;
-    const int64_t N = (int64_t)nx * ny * a.L.nz;
+    const unsigned N = (unsigned)nx * (unsigned)ny * (unsigned)a.L.nz;  // at most 2^31
     const T *src = static_cast<const T *>(a.src);
     CSum cs[3] = {{0, 0}, {0, 0}, {0, 0}};  // mass, sum err^2, sum ref^2
     double maxerr = 0, maxphi = 0, nonfinite = 0;
-    for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (int64_t)gridDim.x * blockDim.x) {
-        const int x = (int)(n % nx);
-        const int64_t r = n / nx;
+    for (unsigned n = blockIdx.x * blockDim.x + threadIdx.x; n < N; n += gridDim.x * blockDim.x) {
+        const int x = (int)(n % (unsigned)nx);
+        const unsigned r = n / (unsigned)nx;
         M g[Q];
-        state3<Q, St, M>(src, a.L, a.edge.kind, x, (int)(r % ny), (int)(r / ny), a.f16, g);
+        state3<Q, St, M>(src, a.L, a.edge.kind, x, (int)(r % (unsigned)ny), (int)(r / (unsigned)ny), a.f16, g);
         double phi = 0;
 #pragma unroll
         for (int i = 0; i < Q; ++i) phi += (double)g[i];
@@ -725,17 +725,7 @@ __global__ __launch_bounds__(256) void macros3_kernel(const MacroArgs a)
             maxerr = fmax(maxerr, fabs(d));
         }
     }
-    block_reduce(cs, maxerr, maxphi, nonfinite);
-    if (threadIdx.x == 0) {
-        double *p = a.partials + (int64_t)blockIdx.x * kMacroPartialDoubles;
-        for (int k = 0; k < 3; ++k) {
-            p[2 * k] = cs[k].s;
-            p[2 * k + 1] = cs[k].c;
-        }
-        p[6] = maxerr;
-        p[7] = maxphi;
-        p[8] = nonfinite;
-    }
+    macros_end(a, cs, maxerr, maxphi, nonfinite);
 }
 
 template <int Q, int MODE>
@@ -877,7 +867,7 @@ hipError_t launch_init3_q(int mode, const InitArgs &a, hipStream_t st)
 }
 
 template <int Q>
-hipError_t launch_macros3_q(int mode, const MacroArgs &a, double *result, hipStream_t st)
+hipError_t launch_macros3_q(int mode, const MacroArgs &a, hipStream_t st)
 {
     const int g = grid_for((int64_t)a.L.nx * a.L.ny * a.L.nz, 256, kMacroBlocks);
     switch (mode) {
@@ -888,8 +878,8 @@ hipError_t launch_macros3_q(int mode, const MacroArgs &a, double *result, hipStr
     default: return hipErrorInvalidValue;
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_macros_finalize(a.partials, g, result, st);
+    if (e != hipSuccess || a.done) return e;
+    return launch_macros_finalize(a, g, st);
 }
 
 template <int Q>
@@ -915,10 +905,10 @@ hipError_t launch_init3(int mode, const InitArgs &a, hipStream_t st)
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_macros3(int mode, const MacroArgs &a, double *result, hipStream_t st)
+hipError_t launch_macros3(int mode, const MacroArgs &a, hipStream_t st)
 {
-    if (a.L.q == 27) return launch_macros3_q<27>(mode, a, result, st);
-    if (a.L.q == 19) return launch_macros3_q<19>(mode, a, result, st);
+    if (a.L.q == 27) return launch_macros3_q<27>(mode, a, st);
+    if (a.L.q == 19) return launch_macros3_q<19>(mode, a, st);
     return hipErrorInvalidValue;
 }
 
