@@ -36,9 +36,14 @@ def bytes_per_lup(mode: str, variable_D: bool) -> int:
 
 
 def launch_bytes_per_lup(mode: str, variable_D: bool, launch: dict) -> float:
-    """Algorithmic bytes per lattice update of the launch that ran: a launch of two fused steps reads
-    the state and the fields once and writes the state once for two updates of every node."""
-    return bytes_per_lup(mode, variable_D) / max(int(launch.get("fuse", 1) or 1), 1)
+    """Algorithmic bytes per lattice update of the launch that ran: a launch of several steps reads
+    the state and the fields once and writes the state once for that many updates of every node."""
+    return bytes_per_lup(mode, variable_D) / max(int(launch.get("steps", launch.get("fuse", 1)) or 1), 1)
+
+
+def launch_of(lbm, s) -> dict:
+    """The launch shape of instance 0 and the steps that one launch of the context takes."""
+    return dict(s.get_launch(), steps=lbm.lbm_launch_steps(s.ctx))
 
 
 def roofline_bound(stores: int) -> str:
@@ -49,7 +54,7 @@ def roofline_bound(stores: int) -> str:
 
 def kernel_hash() -> str:
     h = hashlib.sha256()
-    for name in ("lbm_kernels.hip", "lbm_fused.hip", "lbm_kernel_common.h", "lbm_device.h", "lbm_internal.h",
+    for name in ("lbm_kernels.hip", "lbm_fused.hip", "lbm_strips.h", "lbm_patches.h", "lbm_kernel_common.h", "lbm_device.h", "lbm_internal.h",
                  "lbm_api.hip"):
         with open(os.path.join(ROOT, "paper_2312_10316_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
@@ -88,7 +93,7 @@ def run_mode(mode, n, steps, warmup, torch, W, lbm, Solver, graph=True):
     ms = e0.elapsed_time(e1)
     ref = torch.from_numpy(W.pulse_reference(cfg, f)).cuda()
     st, phi = s.macros(ref=ref, want_phi=True)
-    launch = s.get_launch()
+    launch = launch_of(lbm, s)
     s.close()
     lups = float(n) * n * steps
     return {
@@ -227,7 +232,7 @@ def run_hbm(torch, W, lbm, Solver, n=8192, steps=200, warmup=32, modes=("f32", "
         s = Solver([(lbm.make_params(n, n, f["dx"], f["dt"], cfg.lam, cfg.D, mode), dev)])
         s.step(warmup)
         ms = _timed_steps(torch, s, steps)
-        launch = s.get_launch()
+        launch = launch_of(lbm, s)
         s.close()
         bpl = launch_bytes_per_lup(mode, False, launch)
         mlups = n * n / (ms * 1e-3) / 1e6
@@ -256,13 +261,13 @@ def run_precision_8192(torch, W, lbm, Solver, n=8192, steps=1000):
         s.step(64)
         ms = _timed_steps(torch, s, steps - 64)
         st, phi = s.macros(want_phi=True, raise_nonfinite=False)
-        launch = s.get_launch()
+        launch = launch_of(lbm, s)
         s.close()
         bpl = launch_bytes_per_lup(mode, True, launch)
         r = {"mlups": n * n / (ms * 1e-3) / 1e6, "ms_per_step": ms,
              "hbm_gbps_algorithmic": n * n / (ms * 1e-3) * bpl / 1e9,
              "bytes_per_lup": bpl, "mass_drift": st["mass"] / m0 - 1.0,
-             "nonfinite": st["nonfinite"], "fuse": launch["fuse"]}
+             "nonfinite": st["nonfinite"], "steps_per_launch": launch["steps"]}
         if mode == "f64":
             ref = phi
         else:
@@ -332,7 +337,7 @@ def run_refinement(torch, W, lbm, Solver, sizes=(64, 128, 256, 512, 1024, 2048),
 
 
 def run_flux(torch, W, lbm, Solver, sizes=((2048, 3000), (8192, 200))):
-    """The flux form of the aux term (default launch: two steps per launch) at 2048^2 and 8192^2, FP32 and
+    """The flux form of the aux term (default launch: several steps per launch) at 2048^2 and 8192^2, FP32 and
     FP64: MLUPS, the launch's algorithmic bytes per second against 8 TB/s, and the single-step-equivalent
     rate (the bytes a one-step launch would move for the same updates)."""
     out = {}
@@ -344,7 +349,7 @@ def run_flux(torch, W, lbm, Solver, sizes=((2048, 3000), (8192, 200))):
             s = Solver([(lbm.make_params(n, n, f["dx"], f["dt"], cfg.lam, cfg.D, mode, lbm.LBM_AUX_FLUX), dev)])
             s.step(64)
             ms = _timed_steps(torch, s, steps)
-            launch = s.get_launch()
+            launch = launch_of(lbm, s)
             s.close()
             mlups = n * n / (ms * 1e-3) / 1e6
             bpl = launch_bytes_per_lup(mode, False, launch)
@@ -424,16 +429,17 @@ def run_3d(torch, W, lbm, Solver, q=19, sizes=(64, 128, 256), tp_steps=400):
         for mode in BYTES:
             s = Solver([(mk(mode), fields)])
             if n == sizes[-1] or (len(sizes) > 1 and n == sizes[-2]):
-                stores = s.get_launch()["stores"]
+                stores, fz = s.get_launch()["stores"], lbm.lbm_launch_steps(s.ctx)
                 s.step(64)
                 ms = _timed_steps(torch, s, tp_steps)
                 s.close()
                 s = Solver([(mk(mode), fields)])
                 mlups = n ** 3 / (ms * 1e-3) / 1e6
                 key = "throughput" if n == sizes[-1] else "throughput_cache"
-                out[key][mode] = {"mlups": mlups, "ms_per_step": ms, "bytes_per_lup": BYTES[mode],
-                                  "hbm_gbps_algorithmic": mlups * BYTES[mode] / 1e3,
-                                  "roofline_frac": mlups * BYTES[mode] / 1e3 / HBM_PEAK_GBPS,
+                bpl = BYTES[mode] / fz
+                out[key][mode] = {"mlups": mlups, "ms_per_step": ms, "bytes_per_lup": bpl, "steps_per_launch": fz,
+                                  "hbm_gbps_algorithmic": mlups * bpl / 1e3,
+                                  "roofline_frac": mlups * bpl / 1e3 / HBM_PEAK_GBPS,
                                   "stores": ["non-temporal", "cached", "one buffer in place"][stores]}
             s.step(cfg.steps)
             out["E_r"][mode].append(s.macros(ref=ref)["rms_err"])
@@ -775,7 +781,7 @@ def run_profile_workload(torch, W, lbm, Solver, name, n, steps):
                 s.set_launch(1, 1, tile_width=64)
             s.step(64)
             ms = _timed_steps(torch, s, steps)
-            out[label] = {"mlups": nodes / (ms * 1e-3) / 1e6, "launch": s.get_launch()}
+            out[label] = {"mlups": nodes / (ms * 1e-3) / 1e6, "launch": launch_of(lbm, s)}
         out.update(nodes=nodes, batch=s.get_batch())
         s.close()
     elif name == "adjoint":
@@ -791,7 +797,7 @@ def run_profile_workload(torch, W, lbm, Solver, name, n, steps):
                     s.set_launch(2, 1, tile_width=256)
                 s.step(64)
                 ms = _timed_steps(torch, s, steps)
-                out[f"{mode}_{label}"] = {"mlups": n * n / (ms * 1e-3) / 1e6, "launch": s.get_launch()}
+                out[f"{mode}_{label}"] = {"mlups": n * n / (ms * 1e-3) / 1e6, "launch": launch_of(lbm, s)}
             s.close()
         del dev
         torch.cuda.empty_cache()
@@ -807,7 +813,9 @@ def _workload_kernels(name: str, n: int):
     if name == "batched":
         import workloads as W
         nodes = sum(d.N * d.N for d in W.batched_instances(256))
-        return [("batched_step2_kernel FP32, 256 instances, two steps per launch", r"batched_step2_kernel<2, 0, \d>",
+        return [("batched_strip_kernel FP32, 256 instances, four steps per launch", r"batched_strip_kernel<2, 0>",
+                 nodes * 80.0, 4 * nodes),
+                ("batched_step2_kernel FP32, 256 instances, two steps per launch", r"batched_step2_kernel<2, 0, \d>",
                  nodes * 80.0, 2 * nodes),
                 ("batched_step_kernel FP32, 256 instances, one step per launch", r"batched_step_kernel<2, 0, \d>",
                  nodes * 80.0, nodes)]
@@ -815,13 +823,21 @@ def _workload_kernels(name: str, n: int):
         import workloads as W
         nodes = W.C5_N ** 2
         # state 9 x 4 B and lam 9 x 4 B in, lam 9 x 4 B out, u 8 B and k 4 B in, dL/dD (FP64) read and written
-        return [("adjoint_kernel FP32 (D field, local aux)", r"adjoint_kernel<2, true, false, true>", nodes * 136.0, nodes),
+        return [("adjoint_patch_kernel FP32, four steps per launch", r"adjoint_patch_kernel<2, true, false, true", nodes * (4 * 36.0 + 100.0), 4 * nodes),
+                ("patch_kernel FP32, D field, four images per launch (recomputation)",
+                 r"\bpatch_kernel<2, 0, true, false, 4, \d+, 1, 0, true>", nodes * (36.0 + 12.0 + 4 * 36.0), 4 * nodes),
+                ("patch_kernel FP32, D field (forward, four steps per launch)",
+                 r"\bpatch_kernel<2, 0, true, false, 4, \d+, \d, 0, false>", nodes * 84.0, 4 * nodes),
+                ("adjoint_kernel FP32 (D field, local aux)", r"adjoint_kernel<2, true, false, true>", nodes * 136.0, nodes),
                 ("step_kernel FP32, D field (recomputation, one step per launch)", r"step_kernel<2, 0, true, false, 0, false",
                  nodes * 84.0, nodes),
                 ("step2_kernel FP32, D field (forward, two steps per launch)", r"step2_kernel<2, 0, true, false", nodes * 84.0,
                  2 * nodes)]
     if name == "flux":
-        return [("flux2_kernel FP32, two steps per launch", r"flux2_kernel<2, false, false", float(n) * n * 80.0, 2 * n * n),
+        return [("strip_kernel FP32, flux form, four steps per launch", r"\bstrip_kernel<2, 1, false, false, 4", float(n) * n * 80.0, 4 * n * n),
+                ("strip_kernel FP64, flux form, four steps per launch", r"\bstrip_kernel<0, 1, false, false, 4", float(n) * n * 160.0,
+                 4 * n * n),
+                ("flux2_kernel FP32, two steps per launch", r"flux2_kernel<2, false, false", float(n) * n * 80.0, 2 * n * n),
                 ("flux2_kernel FP64, two steps per launch", r"flux2_kernel<0, false, false", float(n) * n * 160.0,
                  2 * n * n),
                 ("step_kernel FP32, flux form, one step per launch", r"step_kernel<2, 1, false, false", float(n) * n * 80.0,
@@ -947,6 +963,10 @@ def _kernel_label(name: str):
     m = re.search(r"step2_kernel<(\d), (\d), (true|false), (true|false), false, \d, (?:true|false)>", name)
     if m:
         return ("step2", KERNEL_MODES[m.group(1)], int(m.group(2)), m.group(3) == "true", m.group(4) == "true")
+    # four steps per launch: strip_kernel<mode, aux, has_k, has_s, steps, columns per lane, ...>
+    m = re.search(r"\bstrip_kernel<(\d), (\d), (true|false), (true|false), 4, \d", name)
+    if m:
+        return ("strip4", KERNEL_MODES[m.group(1)], int(m.group(2)), m.group(3) == "true", m.group(4) == "true")
     if "copy_kernel" in name:
         return ("copy",)
     return None
@@ -976,8 +996,8 @@ def summarize_trace(trace_dir, out_dir, n, command):
         lab = _kernel_label(r["Name"])
         if lab is None:
             continue
-        mode = lab[1] if lab[0] in ("step", "step2") else "-"
-        steps = 2 if lab[0] == "step2" else 1
+        mode = lab[1] if lab[0] in ("step", "step2", "strip4") else "-"
+        steps = {"step2": 2, "strip4": 4}.get(lab[0], 1)
         avg = float(r["AverageNs"])
         lines.append(f"| {r['Name'][:80]} | {mode} | {r['Calls']} | {avg / 1e3:.2f} | "
                      f"{float(r['TotalDurationNs']) / 1e6:.2f} | " + " | ".join(rates(mode, avg, steps)) + " |")
@@ -1174,15 +1194,15 @@ def main():
         "config": {"workload": f"rotating Gaussian pulse, periodic {args.n}^2, c=10, U0=pi, D=1e-3, Lambda=1/4, "
                                f"{args.warmup}+{args.steps} steps", "N": args.n, "storage": head,
                    "aux": "local (Eq. 16)"},
-        "roofline": {"bound": roofline_bound(stores),
+        "roofline": {"bound": roofline_bound(stores) if r["launch"]["steps"] <= 2 else "valu",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBPS, 4),
                      "traffic": None if traffic is None else round(traffic),
                      "traffic_unit": "bytes/launch filled into L2 from the fabric (rocprofv3 FETCH_SIZE+WRITE_SIZE, "
                                      "copy-calibrated; HBM plus Infinity Cache hits)",
                      "algorithmic_bytes_per_launch": int(n2 * bytes_per_lup(head, False)),
-                     "bytes_per_lup": r["bytes_per_lup"], "lups_per_launch": int(n2 * r["launch"]["fuse"]),
-                     "steps_per_launch": r["launch"]["fuse"],
+                     "bytes_per_lup": r["bytes_per_lup"], "lups_per_launch": int(n2 * r["launch"]["steps"]),
+                     "steps_per_launch": r["launch"]["steps"],
                      "single_step_equivalent_gbps": round(r["mlups"] * bytes_per_lup(head, False) / 1e3, 1),
                      "peak_note": "8 TB/s is the HBM3E spec; a state held in the Infinity Cache is served partly "
                                   "from that cache, whose ceiling is the measured cached copy below",
@@ -1200,9 +1220,10 @@ def main():
         t0 = time.perf_counter()
         hbm = run_hbm(torch, W, lbm, Solver)
         h = hbm["f32"]
-        fz = h["launch"]["fuse"]
-        out["roofline_hbm"] = {"bound": "hbm", "kernel": ("step2_kernel FP32, two steps per launch" if fz == 2 else
-                                                          "step_kernel FP32, one row per wave") + ", non-temporal stores",
+        fz = h["launch"]["steps"]
+        out["roofline_hbm"] = {"bound": "hbm" if fz <= 2 else "valu",
+                               "kernel": {1: "step_kernel FP32, one row per wave", 2: "step2_kernel FP32, two steps per launch"}.get(
+                                   fz, f"strip_kernel FP32, {fz} steps per launch"),
                                "workload": hbm["workload"], "achieved": round(h["achieved_gbps"], 1),
                                "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(h["frac"], 4),
                                "traffic": h["traffic"],

@@ -289,7 +289,13 @@ typedef struct lbm_launch {
                             An odd step count
                             ends with one single step in the context's one-step shape.  Default: 2 for
                             such a single instance of at least 2^18 nodes (2^21 with FP16 storage) and
-                            for such a uniform batch (128 x 16 tiles). */
+                            for such a uniform batch (128 x 16 tiles).
+                            A context whose every instance has the default shape (and the batch its default
+                            policy and blocks) may run more steps per launch than the shape says, bitwise the
+                            same: 4 or 8 for D2Q9 TRT-R (one instance, periodic or between walls, or a uniform
+                            batch with FP64 or FP32 storage), 2 for one D3Q19 or D3Q27 instance with FP64 or
+                            FP32 storage (lbm_launch_steps tells); its 3D single steps may run on another tile
+                            mapping or on one buffer.  Any other shape runs as it is set. */
 } lbm_launch;
 
 /* Sets (inst = -1: every instance) or reads the launch shape; captured step graphs are dropped.
@@ -297,6 +303,9 @@ typedef struct lbm_launch {
  * with xcd_remap 3), LBM_E_STATE for a bad context or instance. */
 int lbm_set_launch(lbm_ctx *ctx, int32_t inst, const lbm_launch *cfg);
 int lbm_get_launch(lbm_ctx *ctx, int32_t inst, lbm_launch *cfg);
+/* Time steps per launch of the context's long runs: 1, 2, 4 or 8.  LBM_E_STATE for a NULL context, LBM_E_ARG
+ * for a NULL pointer. */
+int lbm_launch_steps(lbm_ctx *ctx, int32_t *steps);
 
 /* How a multi-instance context advances its instances each step.
  *   SERIAL:  one kernel launch per instance.

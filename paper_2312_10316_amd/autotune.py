@@ -1,9 +1,9 @@
 """Autotuner for the step launch: tile shape (rows walked per wave, XCD tile order and its row-block
 height, 64- or 256-column tiles), non-temporal or cached stores of the new state, a cap on the waves
 resident per SIMD, one buffer updated in place, two steps per launch (tile width and height), and, for a
-multi-instance context, the
-batch schedule (serial launches, one flat launch, or persistent blocks with a round-robin or
-longest-processing-time assignment of tiles).
+multi-instance context, the batch schedule (serial launches, one flat launch, or persistent blocks with a
+round-robin or longest-processing-time assignment of tiles).  The context's own launch is a candidate too
+(in its default shape a context may run more steps per launch than any set shape does).
 
 Candidates are timed on the caller's own instances with graph-replayed steps; the instances' states
 and step counters are saved first and restored afterwards, so tuning never advances the simulation
@@ -28,7 +28,7 @@ def _key(solver) -> str:
     dev = torch.cuda.get_device_name()
     shapes = [(p.nx, p.ny, p.nz, p.lattice, p.store, p.math, p.aux, p.boundary, p.tau3 not in (0.0, 1.0))
               for p in solver.params]
-    return hashlib.sha256(json.dumps(["launch-v6", dev, shapes]).encode()).hexdigest()[:20]
+    return hashlib.sha256(json.dumps(["launch-v7", dev, shapes]).encode()).hexdigest()[:20]
 
 
 def _fusable_params(p) -> bool:
@@ -103,6 +103,15 @@ def default_candidates(solver) -> list:
     return out
 
 
+def _own_launch(solver) -> list:
+    """The context's current launch as a candidate, if one tuple holds it for every instance."""
+    own = [solver.get_launch(k) for k in range(len(solver.params))]
+    if any(o != own[0] for o in own):
+        return []
+    o, b = own[0], solver.get_batch() if len(own) > 1 else {"policy": L.LBM_BATCH_SERIAL, "blocks": 0}
+    return [(o["rows"], o["xcd_remap"], o["xcd_rows"], o["tile_width"], o["max_waves"], o["stores"], b["policy"], b["blocks"], o["fuse"])]
+
+
 def _apply(solver, cand) -> None:
     rows, remap, h, width, cap, stores, policy, blocks, fuse = (tuple(cand) + (1,))[:9]
     solver.set_launch(rows, remap, tile_width=width, max_waves=cap, xcd_rows=h, stores=stores, fuse=fuse)
@@ -152,7 +161,7 @@ def tune(solver, candidates: Optional[Iterable] = None, steps: int = 64, reps: i
     old_batch = solver.get_batch() if n > 1 else None
     times = {}
     try:
-        for cand in (candidates or default_candidates(solver)):
+        for cand in (candidates or dict.fromkeys(_own_launch(solver) + default_candidates(solver))):
             _apply(solver, cand)
             times[json.dumps(list(cand))] = _time(solver, steps, reps)
     finally:

@@ -643,11 +643,11 @@ int build_strip_schedule(lbm_ctx *c)
     return e == hipSuccess ? LBM_OK : hip_fail(e, "uploading strip work items");
 }
 
-// Strips and the gapless 3D kernel go with the default launch shape (and batch schedule), and again when the
-// caller sets those.
+// Strips and the gapless 3D kernel go with the default launch shape (and batch policy and blocks; the cap on the
+// waves of one-step launches is not theirs), and again when the caller sets those.
 void update_strips(lbm_ctx *c)
 {
-    c->strips_on = c->strips.rows > 0 && std::memcmp(&c->batch, &c->strips_batch, sizeof c->batch) == 0;
+    c->strips_on = c->strips.rows > 0 && c->batch.policy == c->strips_batch.policy && c->batch.blocks == c->strips_batch.blocks;
     for (int k = 0; k < (int)c->inst.size(); ++k) {
         Instance &in = c->inst[k];
         lbm_launch now = {};
@@ -1611,6 +1611,15 @@ int lbm_set_batch(lbm_ctx *c, const lbm_batch *cfg)
     c->batch = *cfg;
     update_strips(c);
     return refresh_tables(c);
+}
+
+int lbm_launch_steps(lbm_ctx *c, int32_t *steps)
+{
+    g_err[0] = 0;
+    if (!c) return fail(LBM_E_STATE, "lbm_launch_steps: NULL context");
+    if (!steps) return fail(LBM_E_ARG, "lbm_launch_steps: steps is NULL");
+    *steps = c->strips_on ? c->strips.steps : fused(c) ? 2 : 1;
+    return LBM_OK;
 }
 
 int lbm_get_batch(lbm_ctx *c, lbm_batch *cfg)

@@ -78,7 +78,7 @@ EXPORTS = ["lbm_workspace_size", "lbm_init", "lbm_step", "lbm_set_velocity", "lb
            "lbm_state_save", "lbm_state_load", "lbm_set_launch", "lbm_get_launch", "lbm_set_batch", "lbm_get_batch",
            "lbm_adjoint_bytes", "lbm_adjoint_seed", "lbm_adjoint_step", "lbm_adjoint_init", "lbm_bench_copy", "lbm_free",
            "lbm_pitch", "lbm_last_error", "lbm_abi_version", "lbm_set_diffusion", "lbm_adjoint_segment",
-           "lbm_bench_copy_cached", "lbm_macros_static"]
+           "lbm_bench_copy_cached", "lbm_macros_static", "lbm_launch_steps"]
 
 
 def pitch_of(p: "lbm_params") -> int:
@@ -117,6 +117,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.lbm_bench_copy.argtypes = [P, P, SZ, P]
     lib.lbm_bench_copy_cached.argtypes = [P, P, SZ, P]
     lib.lbm_set_diffusion.argtypes = [P, I32, P]
+    lib.lbm_launch_steps.argtypes = [P, ctypes.POINTER(I32)]
     lib.lbm_adjoint_segment.argtypes = [P, I32, P, I32, P, P, P]
     lib.lbm_free.argtypes = [P]
     lib.lbm_last_error.argtypes = []
@@ -242,6 +243,13 @@ def lbm_macros_static(ctx, inst: int = 0, phi_out: Optional[torch.Tensor] = None
     d = st.as_dict()
     d["status"] = rc
     return d
+
+
+def lbm_launch_steps(ctx) -> int:
+    """Time steps per launch of the context's long runs."""
+    out = ctypes.c_int32()
+    _check(lib().lbm_launch_steps(ctx, ctypes.byref(out)))
+    return out.value
 
 
 def lbm_populations(ctx, inst: int, out: torch.Tensor) -> None:
