@@ -723,6 +723,8 @@ def _kernel3_label(name: str):
     other -> None."""
     import re
     m = re.search(r"step3_kernel<(19|27), (\d), (\d), false, false(?:, \d)?(?:, (?:true|false))?(?:, \d)?>", name)
+    if not m:  # two steps per launch; the gapless single step
+        m = re.search(r"step3(?:x2|_flat)_kernel<(19|27), (\d), (\d), false, false[,>]", name)
     if m:
         return (f"d3q{m.group(1)}", KERNEL_MODES[m.group(2)])
     if "copy_kernel" in name:

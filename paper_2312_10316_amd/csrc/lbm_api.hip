@@ -451,7 +451,7 @@ InstDesc desc_of(const Instance &in)
 // Long runs replay a captured graph of kGraphSteps steps (an even number of launches, so every buffer
 // returns to its role); one graph per buffer parity, dropped whenever a descriptor or the schedule changes.
 constexpr int kGraphSteps = 32;
-static_assert(kGraphSteps % 4 == 0 && kGraphSteps % (2 * kStripSteps) == 0 && kGraphSteps % (2 * kFluxStripSteps) == 0,
+static_assert(kGraphSteps % 16 == 0 && kGraphSteps % (2 * kStripSteps) == 0 && kGraphSteps % (2 * kFluxStripSteps) == 0,
               "a graph replay must keep the buffer parity");
 
 // Device scratch of lbm_macros_static: the per-block partial sums of the diagnostics reduction

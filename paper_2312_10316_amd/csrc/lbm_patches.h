@@ -23,8 +23,8 @@ namespace {
 // of H rows.  Two rows per wave halve the exchange and recompute less (24 rows for 18, not 16 for 10), at one
 // block per CU instead of two.  What bounds it: the launch (about 2 us in a replayed graph) and T times the
 // latency of a node update and the exchange.  Us per step, strips / patches: FP64 64^2 1.96 / 1.17, FP32 128^2
-// 1.80 / 0.99, 256^2 2.11 / 1.33, 512^2 3.73 / 2.62, 1000^2 7.15 / 5.79,
-// FP16 with stochastic rounding 300^2 3.96 / 2.14.
+// 1.80 / 0.99, 256^2 2.11 / 1.33, 512^2 3.73 / 2.62, 1000^2 7.15 / 5.79, FP16 with
+// stochastic rounding 300^2 3.96 / 2.14.
 // Bitwise T single steps, as the strips.
 // IMG: every step's state is stored, image_bytes apart from buf[parity ^ 1] on (the adjoint's recomputation).
 template <int MODE, int AUX, bool HAS_K, bool HAS_S, int T, int NW, int R, int BC, bool IMG = false>

@@ -19,16 +19,18 @@
 // FP16 storage on large lattices gives each lane two adjacent columns (strips of 120 columns: fewer
 // lanes lost at the ends, half the lane shifts, one 4-byte access where 2-byte ones were).
 //
-// What bounds it: VALU issue for FP32 (2048^2: 97 vector instructions per node and step, issued 90 % of
-// the time), memory and VALU about equally for FP64 (188 VGPRs, two waves per SIMD).  The rows before the
+// What bounds it: VALU issue for FP32 (2048^2: 97 vector instructions per node row and step, 133 per node and
+// step with the recomputed rows and lanes, busy on 0.68 of the launch's cycles with two waves per SIMD), memory
+// and the latency of two waves per SIMD for FP64 (188 VGPRs; VALU on 0.45 of the cycles, 4.9 TB/s).  The rows before the
 // first output row run in a loop of their own with the steps that have no row yet skipped by uniform
 // branches; as straight code they had cost 40 VGPRs (FP32 140 -> 100).
 // Against two steps per launch through an LDS ring (lbm_fused.hip): FP32 2048^2 131k -> 206k MLUPS, 8192^2
-// 140k -> 223k, 256^2 24k -> 31k, FP64 2048^2 64k -> 118k, 8192^2 69k -> 126k; flux form FP32 2048^2 92k ->
-// 164k, 8192^2 114k -> 198k, FP64 4096^2 57k -> 83k (T = 2, 56 columns: 63k); FP16 (VALU issue both ways) 8192^2 with D 180k -> 210k, with stochastic rounding 141k -> 150k,
-// 1024^2 118k -> 139k.  Why T = 4: 56 columns start every strip on a 32-byte boundary; three steps need 58 (or waste
-// two lanes) and measured 135k at 2048^2 FP32, because the stores of neighbouring strips then share
-// 32-byte sectors; with six the carried values no longer fit the registers of FP64.
+// 140k -> 223k, FP64 2048^2 64k -> 118k, 8192^2 69k -> 126k; flux form FP32 2048^2 92k -> 164k, 8192^2 114k ->
+// 198k, FP64 4096^2 57k -> 83k (T = 2, 56 columns: 63k); FP16 (VALU issue both ways) 8192^2 with D 180k ->
+// 210k, with stochastic rounding 141k -> 150k.  Lattices up to about 1200^2 run on patches (lbm_patches.h).  Why
+// T = 4: 56 columns start every strip on a 32-byte boundary; three steps need 58 (or waste two lanes) and
+// measured 135k at 2048^2 FP32, because the stores of neighbouring strips then share 32-byte sectors; with six
+// the carried values no longer fit the registers of FP64.
 #pragma once
 
 #include <type_traits>
