@@ -244,7 +244,7 @@ __device__ inline void macros_merge(const double *partials, int nblocks, double 
 }
 
 // End of a diagnostics kernel: the block's partials, and with a.done the merge by the last block to finish (a
-// second launch is 4 us of a call on a small lattice).  The partials have left the wave (vmcnt 0) before the
+// second launch is 3 us of a call on a small lattice).  The partials have left the wave (vmcnt 0) before the
 // block is counted; an agent-scope release would write back every dirty line of the XCD's L2 (a batch's 32^2 to
 // 512^2 lattices: 13.3 us per launch, 11.4 so).  The last block leaves the count at 0 for the next launch.
 __device__ inline void macros_end(const MacroArgs &a, CSum (&cs)[3], double maxerr, double maxphi, double nonfinite)

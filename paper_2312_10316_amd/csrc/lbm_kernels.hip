@@ -790,9 +790,10 @@ hipError_t launch_prep(int mode, const PrepArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_macros(int mode, const MacroArgs &a, hipStream_t st)
+hipError_t launch_macros(int mode, MacroArgs a, hipStream_t st)
 {
     const int g = grid_for((int64_t)a.L.nx * a.L.ny, 256, kMacroBlocks);
+    if (g > kMacroFusedBlocks) a.done = nullptr;
     switch (mode) {
     case MODE_F64_F64: macros_kernel<MODE_F64_F64><<<g, 256, 0, st>>>(a); break;
     case MODE_F64_F32: macros_kernel<MODE_F64_F32><<<g, 256, 0, st>>>(a); break;
