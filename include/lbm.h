@@ -167,6 +167,10 @@ int lbm_init(lbm_ctx **ctx, int32_t n_inst, const lbm_params *p, const lbm_field
  * S, dSdt: host arrays [n_inst] of device FP64 [ny][nx] source S and its time derivative, held
  *         constant over this call's steps, or NULL (both) for no source.  An entry may be NULL for an
  *         instance without a source; dSdt entries may be NULL (zero derivative).
+ * Under HIP graph capture of the context's stream, fewer than 64 steps are enqueued with the steps per launch
+ * that lbm_get_launch reports (fuse).  Every launch moves the state to the other buffer, so a captured call
+ * of an even number of launches (nsteps a multiple of 2, or of 4 with fuse = 2) can be replayed any number of
+ * times; the host's step counters do not see the replays.
  * If a launch fails (LBM_E_HIP), the step counters include only the steps enqueued in full before
  * the failure, and the populations of an instance are unspecified from then on (reload a state with
  * lbm_state_load). */

@@ -968,6 +968,18 @@ int enqueue_strips(lbm_ctx *c, const StripLaunch &how, hipStream_t st)
     return LBM_OK;
 }
 
+// Whether the caller records the context's stream into a graph of its own.
+bool recording(const lbm_ctx *c)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (!c->stream) return false;  // the default stream cannot be recorded
+    if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
 // Returns the graph of kGraphSteps steps for the current buffer parity, capturing it if needed.
 int graph_for(lbm_ctx *c, hipGraphExec_t *out)
 {
@@ -1320,7 +1332,9 @@ int lbm_step(lbm_ctx *c, int32_t nsteps, const double *const *ux, const double *
             if (e != hipSuccess) return account(hip_fail(e, "hipGraphLaunch"));
         }
     }
-    if (c->strips_on)
+    // A graph that the caller records is replayed from the buffer it started from, so it must hold an even number
+    // of launches; with the steps per launch that the shape says, the caller can see to that.
+    if (c->strips_on && left >= 2 && !recording(c))
         for (const StripLaunch &how : {c->strips, rest_of(c->strips)})
             for (; how.steps > 0 && left >= how.steps; left -= how.steps) {
                 rc = enqueue_strips(c, how, c->stream);
