@@ -311,6 +311,25 @@ int lbm_get_launch(lbm_ctx *ctx, int32_t inst, lbm_launch *cfg);
  * for a NULL pointer. */
 int lbm_launch_steps(lbm_ctx *ctx, int32_t *steps);
 
+/* What the steps of the context's long runs really run on, which a default launch shape does not tell (of
+ * instance 0, where they differ):
+ *   TILES:   the kernels that lbm_get_launch describes (on one buffer in place where stores is 2);
+ *   STRIPS:  several D2Q9 steps per launch on strips that one wave owns;
+ *   PATCHES: several D2Q9 steps per launch on patches of `waves` waves;
+ *   PLANES:  two 3D steps per launch;
+ *   GAPLESS: single 3D steps with the nodes dealt to the lanes without gaps. */
+enum lbm_route_kind { LBM_ROUTE_TILES = 0, LBM_ROUTE_STRIPS = 1, LBM_ROUTE_PATCHES = 2, LBM_ROUTE_PLANES = 3, LBM_ROUTE_GAPLESS = 4 };
+typedef struct lbm_route {
+    int32_t kind;   /* enum lbm_route_kind */
+    int32_t steps;  /* time steps per launch */
+    int32_t rows;   /* rows of a tile or strip, rows per wave of a patch, or planes of a 3D tile */
+    int32_t cols;   /* output columns of a tile, strip or patch */
+    int32_t waves;  /* waves of a patch, else 0 */
+    int32_t stores; /* as lbm_launch.stores */
+} lbm_route;
+/* LBM_E_STATE for a NULL context, LBM_E_ARG for a NULL pointer. */
+int lbm_launch_route(lbm_ctx *ctx, lbm_route *route);
+
 /* How a multi-instance context advances its instances each step.
  *   SERIAL:  one kernel launch per instance.
  *   FLAT:    one launch for all instances, one 256-thread block per tile (tiles of all instances in

@@ -1636,6 +1636,33 @@ int lbm_launch_steps(lbm_ctx *c, int32_t *steps)
     return LBM_OK;
 }
 
+int lbm_launch_route(lbm_ctx *c, lbm_route *route)
+{
+    g_err[0] = 0;
+    if (!c) return fail(LBM_E_STATE, "lbm_launch_route: NULL context");
+    if (!route) return fail(LBM_E_ARG, "lbm_launch_route: route is NULL");
+    const Instance &in = c->inst[0];
+    const StripLaunch &s = c->strips;
+    *route = lbm_route{};
+    if (c->strips_on) {
+        route->kind = is3d(in) ? LBM_ROUTE_PLANES : s.patch > 0 ? LBM_ROUTE_PATCHES : LBM_ROUTE_STRIPS;
+        route->steps = s.steps;
+        route->rows = s.rows;
+        route->waves = s.patch;
+        const bool flux = in.p.aux == LBM_AUX_FLUX;
+        route->cols = is3d(in) ? s.cols : strip_width(flux ? 2 * s.steps : s.steps, s.cols);
+        route->stores = s.cached || s.patch > 0 || c->inst.size() > 1 ? 1 : 0;
+        return LBM_OK;
+    }
+    const Launch &lc = in.lc;
+    route->kind = lc.flat && lc.stores != 2 ? LBM_ROUTE_GAPLESS : LBM_ROUTE_TILES;
+    route->steps = fused(c) ? 2 : 1;
+    route->rows = lc.rows;
+    route->cols = lc.fuse == 2 ? lc.fuse_width : (lc.wide ? 256 : 64);
+    route->stores = lc.stores;
+    return LBM_OK;
+}
+
 int lbm_get_batch(lbm_ctx *c, lbm_batch *cfg)
 {
     g_err[0] = 0;

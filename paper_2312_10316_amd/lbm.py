@@ -72,13 +72,19 @@ class lbm_batch(ctypes.Structure):
     _fields_ = [("policy", ctypes.c_int32), ("blocks", ctypes.c_int32), ("max_waves", ctypes.c_int32)]
 
 
+class lbm_route(ctypes.Structure):
+    _fields_ = [("kind", ctypes.c_int32), ("steps", ctypes.c_int32), ("rows", ctypes.c_int32), ("cols", ctypes.c_int32),
+                ("waves", ctypes.c_int32), ("stores", ctypes.c_int32)]
+
+
+LBM_ROUTE_TILES, LBM_ROUTE_STRIPS, LBM_ROUTE_PATCHES, LBM_ROUTE_PLANES, LBM_ROUTE_GAPLESS = 0, 1, 2, 3, 4
 LBM_BATCH_SERIAL, LBM_BATCH_FLAT, LBM_BATCH_STRIDED, LBM_BATCH_LPT = 0, 1, 2, 3
 
 EXPORTS = ["lbm_workspace_size", "lbm_init", "lbm_step", "lbm_set_velocity", "lbm_set_dirichlet", "lbm_macros", "lbm_populations", "lbm_state_bytes",
            "lbm_state_save", "lbm_state_load", "lbm_set_launch", "lbm_get_launch", "lbm_set_batch", "lbm_get_batch",
            "lbm_adjoint_bytes", "lbm_adjoint_seed", "lbm_adjoint_step", "lbm_adjoint_init", "lbm_bench_copy", "lbm_free",
            "lbm_pitch", "lbm_last_error", "lbm_abi_version", "lbm_set_diffusion", "lbm_adjoint_segment",
-           "lbm_bench_copy_cached", "lbm_macros_static", "lbm_launch_steps"]
+           "lbm_bench_copy_cached", "lbm_macros_static", "lbm_launch_steps", "lbm_launch_route"]
 
 
 def pitch_of(p: "lbm_params") -> int:
@@ -118,6 +124,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.lbm_bench_copy_cached.argtypes = [P, P, SZ, P]
     lib.lbm_set_diffusion.argtypes = [P, I32, P]
     lib.lbm_launch_steps.argtypes = [P, ctypes.POINTER(I32)]
+    lib.lbm_launch_route.argtypes = [P, ctypes.POINTER(lbm_route)]
     lib.lbm_adjoint_segment.argtypes = [P, I32, P, I32, P, P, P]
     lib.lbm_free.argtypes = [P]
     lib.lbm_last_error.argtypes = []
@@ -250,6 +257,13 @@ def lbm_launch_steps(ctx) -> int:
     out = ctypes.c_int32()
     _check(lib().lbm_launch_steps(ctx, ctypes.byref(out)))
     return out.value
+
+
+def lbm_launch_route(ctx) -> dict:
+    """What the steps of the context's long runs run on (LBM_ROUTE_*, steps, rows, cols, waves, stores)."""
+    out = lbm_route()
+    _check(lib().lbm_launch_route(ctx, ctypes.byref(out)))
+    return {k: getattr(out, k) for k, _ in out._fields_}
 
 
 def lbm_populations(ctx, inst: int, out: torch.Tensor) -> None:
