@@ -219,6 +219,27 @@ Launch fused_default(const lbm_params &p, int mode)
     return lc;
 }
 
+// Rows of a strip of two columns per lane, of which two waves run on a SIMD, and in `units` the node rows of the
+// fullest SIMD, which is the time of the launch (8192^2 FP16 with D 0.13 us per unit whatever the rows; stochastic
+// rounding 0.19): every strip computes T H + T (T - 1) node rows, so one strip too many costs a whole one.  With 48
+// rows throughout (3472^2: 2117 strips) 75.4 us per step of FP16 and 111 with stochastic rounding, with 50 (2030
+// strips, two per SIMD) 54.5 and 79.5; 5000^2 122 and 180, with 52 rows 107 and 158; 8192^2 with D 320, with 70 rows
+// 307.
+int pair_rows(int nx, int ny, int64_t &units)
+{
+    constexpr int V = strip_width(kStripSteps, 2);
+    const int64_t ns = (nx + V - 1) / V;
+    int best = 0;
+    for (int h = 32; h <= 80; ++h) {
+        const int64_t t = (ns * ((ny + h - 1) / h) + 1023) / 1024 * (kStripSteps * h + kStripSteps * (kStripSteps - 1));
+        if (best == 0 || t < units) {
+            best = h;
+            units = t;
+        }
+    }
+    return best;
+}
+
 // Rows of a strip of T steps on an nx x ny lattice.  A strip of H rows computes T H + T (T - 1) node rows
 // (T H + 2 T (T - 1) in the flux form; each step's rows beyond the strip's are recomputed by its
 // neighbours), so tall strips waste less and short ones fill the chip.  Time of a launch in units of one
@@ -802,10 +823,14 @@ StripLaunch rest_of(StripLaunch s)
 // FP64 8192^2 69k / 126k; flux form FP32 2048^2 92k / 164k, 512^2 32k / 47k, FP64 4096^2
 // 57k / 83k; walls FP32 1000 x 500 63k / 104k (patches 118k); 128 instances of 32^2 .. 512^2 FP32
 // 105k / 178k.
-// Columns per lane: two for FP16 from 12e6 nodes on (even nx, local or no aux term), 48 rows (8192^2 with D
-// 180k / 210k, one column 196k; 4096^2 166k / 194k, one column 171k).  FP16 states of narrow lattices that
+// Columns per lane: two for FP16 from 12e6 nodes on (even nx, local or no aux term; 8192^2 with D 180k / 219k, one
+// column 196k; 4096^2 166k / 194k, one column 171k).  FP16 states of narrow lattices that
 // fill 512-column tiles stay on two-step tiles (2048^2 203k, strips 190k; flux form 132k, 124k), as do those
-// with stochastic rounding below 12e6 nodes (2048^2 160k, strips 134k; 1024^2 level).
+// with stochastic rounding below 12e6 nodes (2048^2 160k, strips 134k; 1024^2 level).  Beyond, stochastic rounding
+// takes the faster of strips (6 us and 0.172 us per unit of pair_rows, 0.186 with D) and two-step tiles (5.9e-6 us
+// per node that the tiles cover, 7.3e-6 with D, a tenth more up to 2048 columns): us per step, tiles / strips,
+// 8192^2 391 / 408 (pulse; 421 / 408 on a dense field) and with D 490 / 443; 4096^2 109 / 112 and 129 / 121; 6100 x
+// 2000 72 / 79; 300 x 60000 206 / 136; 512 x 60000 220 / 222; 2000 x 20000 290 / 240.
 // Stores: the default launch's kind (cached within the Infinity Cache); FP32 and FP16 states of more
 // than twice that cache are stored cached too, which merges the lines that neighbouring strips share
 // (FP32 8192^2 208k streaming / 220k cached, 4096^2 206k / 216k, FP16 8192^2 218k / 223k; 2048^2 FP32, 1.3
@@ -838,11 +863,18 @@ StripLaunch strip_default(const lbm_ctx *c, size_t touched, bool batch_fuses)
     if (in.p.ny < 16) return s;
     const bool walls = in.p.boundary == LBM_BC_WALLS, flux = in.p.aux == LBM_AUX_FLUX;
     const bool pairs = f16 && !walls && !flux && in.p.nx % 2 == 0 && nodes >= 12000000;
-    if (in.mode == MODE_F16SR_F32 && !pairs) return s;
+    int64_t units = 0;
+    const int prows = pairs ? pair_rows(in.p.nx, in.p.ny, units) : 0;
+    if (in.mode == MODE_F16SR_F32) {
+        if (!pairs) return s;
+        const int64_t covered = (int64_t)((in.p.nx + in.lc.fuse_width - 1) / in.lc.fuse_width) * in.lc.fuse_width * in.p.ny;
+        const double tiles = (double)covered * (in.has_D ? 7.3e-6 : 5.9e-6) * (in.p.nx <= 2048 ? 1.1 : 1.0);
+        if (tiles < 6.0 + (in.has_D ? 0.186 : 0.172) * (double)units) return s;
+    }
     if (walls && in.mode == MODE_F64_F32) return s;
     if (f16 && !pairs && !walls && in.p.nx <= 2048 && (in.p.nx + 511) / 512 * 512 - in.p.nx <= 64 && nodes >= fuse_min_nodes(in.mode))
         return s;
-    s.rows = pairs ? 48 : strip_rows(in.mode, in.p.nx, in.p.ny, flux);
+    s.rows = pairs ? prows : strip_rows(in.mode, in.p.nx, in.p.ny, flux);
     s.cols = pairs ? 2 : 1;
     s.steps = flux ? kFluxStripSteps : kStripSteps;
     if (in.mode == MODE_F32_F32 && !flux && !walls) s.lds_reserve = lds_reserve_for(nodes >= 7000000 ? 2 : 3, c->lds_per_cu);

@@ -65,6 +65,31 @@ def test_periodic_strips(mode, nx, ny, stores, cols):
         compare(mode, nx, ny, aux, var, want, (4, 7, 70), source=source)
 
 
+@pytest.mark.parametrize("nx,ny,var", [(120, 101700, False), (4096, 4096, True), (300, 43000, False)])
+def test_stochastic_rounding_on_strips(nx, ny, var):
+    compare("f16sr", nx, ny, LOCAL, var, dict(kind=STRIPS, steps=4, cols=120), (4, 7, 70))
+
+
+@pytest.mark.parametrize("nx,ny,var", [(3472, 3472, False), (6100, 2000, False), (4096, 4096, False), (8192, 8192, False),
+                                       (500, 30000, False)])
+def test_stochastic_rounding_on_tiles(nx, ny, var):
+    """From 12e6 nodes on stochastic rounding without a D field is faster on two-step tiles (3472^2: 83 us per step, on
+    strips of 48 rows 111), unless the tiles hang over the lattice."""
+    f = fields(nx, ny, var=var)
+    s = Solver([(lbm.make_params(nx, ny, 1.0, 1.0, 0.25, 0.02, "f16sr", phi_ref=1.0), f)])
+    got = lbm.lbm_launch_route(s.ctx)
+    assert (got["kind"], got["steps"]) == (lbm.LBM_ROUTE_TILES, 2), got
+
+
+@pytest.mark.parametrize("nx,ny", [(3472, 3472), (5000, 5000), (6100, 2000)])
+def test_rows_of_two_column_strips(nx, ny):
+    """No SIMD gets a strip more than the others for the last few strips: 120-column strips in whole rounds of 1024."""
+    s = Solver([(lbm.make_params(nx, ny, 1.0, 1.0, 0.25, 0.02, "f16s", phi_ref=1.0), fields(nx, ny))])
+    got = lbm.lbm_launch_route(s.ctx)
+    strips = -(-nx // 120) * -(-ny // got["rows"])
+    assert got["cols"] == 120 and strips / 1024 > 0.9 * -(-strips // 1024)
+
+
 @pytest.mark.parametrize("mode,nx,ny,stores", [("f32", 2048, 2048, 0), ("f64", 1600, 1601, 0), ("f64s_f32m", 1600, 1601, 0),
                                                ("f16s", 2901, 2900, 0), ("f32", 1009, 1200, 1), ("f16s", 1009, 1200, 1)])
 def test_flux_strips(mode, nx, ny, stores):
