@@ -808,6 +808,28 @@ StripLaunch patch_default(const Instance &in)
     return in.mode != MODE_F64_F32 && rounds ? take(4, 12, 2) : take(4, 16, 1);
 }
 
+// Lattices of so few rows that patches hang over them, in more blocks than run at once: the launch pays for the
+// patches' rows, the step kernels (the two-step ones of many nodes) for the lattice's.  Us per step of a patch launch
+// of b blocks and of the step kernels on N nodes, fitted over 3 .. 31 rows of 3000 .. 500000 columns, on which the
+// rule takes the slower one by at most 9 % (mean 0.5 %): FP32 1.3 + 0.0023 b and 3.15 + 7.3e-6 N (100000 x 3 4.7 /
+// 4.25, 100000 x 5 4.8 / 6.1), FP16 1.5 + 0.0031 b (two rows per wave 2.9 + 0.0038 b) and 2.8 + 7.5e-6 N (150000 x 3
+// 9.2 / 6.4), with stochastic rounding 1.9 + 0.0039 b (2.8 + 0.0063 b) and 3.2 + 7.8e-6 N (200000 x 3 14.6 / 8.0, 50000
+// x 25 12.9 / 12.2).  FP64 storage, and FP32 between walls (100000 x 3 5.8 / 7.1), are the faster on patches on all of
+// them.  From 16 rows on the others have strips as well.
+bool patches_overhang(const Instance &in, const StripLaunch &s)
+{
+    const bool sr = in.mode == MODE_F16SR_F32, f16 = is_f16_mode(in.mode);
+    if ((in.mode != MODE_F32_F32 && !f16) || in.p.ny >= (sr ? 40 : 16)) return false;
+    if (!f16 && in.p.boundary != LBM_BC_PERIODIC) return false;
+    const int V = strip_width(s.steps, 1), H = s.patch * s.rows - 2 * (s.steps - 1);
+    const int64_t b = (int64_t)((in.p.nx + V - 1) / V) * ((in.p.ny + H - 1) / H);
+    if (b <= 256) return false;
+    const double patches = s.rows == 2 ? (sr ? 2.8 + 0.0063 * b : f16 ? 2.9 + 0.0038 * b : 2.1 + 0.0031 * b)
+                                       : (sr ? 1.9 + 0.0039 * b : f16 ? 1.5 + 0.0031 * b : 1.3 + 0.0023 * b);
+    const double n = (double)in.p.nx * in.p.ny, tiles = sr ? 3.2 + 7.8e-6 * n : f16 ? 2.8 + 7.5e-6 * n : 3.15 + 7.3e-6 * n;
+    return patches > tiles;
+}
+
 // Launch for the steps that a multiple of s.steps leaves over: eight-step patches have four-step ones.
 StripLaunch rest_of(StripLaunch s)
 {
@@ -858,6 +880,7 @@ StripLaunch strip_default(const lbm_ctx *c, size_t touched, bool batch_fuses)
         return s;
     if (in.p.aux != LBM_AUX_FLUX) {
         s = patch_default(in);
+        if (s.patch > 0 && patches_overhang(in, s)) s = StripLaunch{};
         if (s.patch > 0) return s;
     }
     if (in.p.ny < 16) return s;

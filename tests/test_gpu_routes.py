@@ -113,6 +113,21 @@ def test_periodic_patches(mode, nx, ny, steps, rows, waves):
         compare(mode, nx, ny, aux, var, want, (8, 13, 75), source=source)
 
 
+@pytest.mark.parametrize("mode,nx,ny,boundary", [("f32", 100000, 3, lbm.LBM_BC_PERIODIC), ("f16s", 150000, 3, lbm.LBM_BC_PERIODIC),
+                                                 ("f16sr", 200000, 3, lbm.LBM_BC_PERIODIC), ("f16sr", 150000, 6, lbm.LBM_BC_PERIODIC),
+                                                 ("f16s", 100000, 3, lbm.LBM_BC_WALLS), ("f16sr", 100000, 4, lbm.LBM_BC_WALLS)])
+def test_few_rows_stay_on_tiles(mode, nx, ny, boundary):
+    """Patches of 10 output rows on a lattice of 3 took up to 1.8 times the step kernels' time."""
+    compare(mode, nx, ny, LOCAL, False, dict(kind=lbm.LBM_ROUTE_TILES), (4, 7), boundary=boundary)
+
+
+@pytest.mark.parametrize("mode,nx,ny", [(m, nx, ny) for m in ("f64", "f64s_f32m", "f32", "f16s", "f16sr")
+                                        for nx, ny in ((2000, 3), (10000, 7), (5000, 12))]
+                         + [("f32", 20000, 7), ("f16s", 20000, 7), ("f16sr", 20000, 7), ("f64s_f32m", 100000, 3)])
+def test_few_rows_on_patches(mode, nx, ny):
+    compare(mode, nx, ny, LOCAL, True, dict(kind=PATCHES), (8, 13))
+
+
 @pytest.mark.parametrize("mode", ["f64", "f64s_f32m", "f32", "f16s", "f16sr"])
 @pytest.mark.parametrize("nx,ny,steps,waves", [(64, 64, 8, 16), (200, 150, 4, 12), (400, 200, 4, 16)])
 def test_patches_between_walls(mode, nx, ny, steps, waves):
