@@ -516,7 +516,6 @@ struct lbm_ctx {
     double *partials = nullptr;
     double *result = nullptr;
     int *flag = nullptr;
-    unsigned *macros_done = nullptr;  // finished blocks of a diagnostics launch (device)
     double *host_result = nullptr;    // this context's slot of pinned host memory, or nullptr: result and a copy
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     int device = -1;                  // the device current at lbm_init (its stream's device)
@@ -1166,7 +1165,6 @@ int lbm_init(lbm_ctx **out, int32_t n_inst, const lbm_params *p, const lbm_field
     c->partials = reinterpret_cast<double *>(w);
     c->result = reinterpret_cast<double *>(w + kPartialBytes);
     c->flag = reinterpret_cast<int *>(w + kPartialBytes + 256);
-    c->macros_done = reinterpret_cast<unsigned *>(c->flag) + 2;
     c->host_result = take_result_slot();
     w += align_up(kScratchBytes, kAlign);
     c->inst.resize(n_inst);
@@ -1408,10 +1406,8 @@ int lbm_step(lbm_ctx *c, int32_t nsteps, const double *const *ux, const double *
 }
 
 namespace {
-// The diagnostics of lbm_macros with the reduction's per-block partials and result in `partials` and
-// `result` (device).
-// `result` on the host (a pinned slot) is merged by the kernel itself and read after the synchronization; on the
-// device a second launch merges and a copy reads it (the scratch that contexts share has no count of its own).
+// The diagnostics of lbm_macros with the reduction's per-block partials in `partials` (device) and its result in
+// `result`: on the host (a pinned slot), read after the synchronization, or on the device, which a copy reads.
 int macros_into(lbm_ctx *c, int32_t inst, double *phi_out, const double *ref, lbm_stats *out, double *partials,
                 double *result, bool on_host)
 {
@@ -1427,7 +1423,6 @@ int macros_into(lbm_ctx *c, int32_t inst, double *phi_out, const double *ref, lb
     a.edge.kind = in.lc.stores == 2 && c->parity == 1 ? 3 : in.p.boundary;  // 3: one buffer after a streaming step
     a.partials = partials;
     a.result = result;
-    a.done = on_host ? c->macros_done : nullptr;
     hipError_t e = is3d(in) ? launch_macros3(in.mode, a, c->stream) : launch_macros(in.mode, a, c->stream);
     if (e != hipSuccess) return hip_fail(e, "macros kernel launch");
     double r[6];

@@ -167,15 +167,10 @@ struct MacroArgs {
     EdgeArgs edge;
     double *partials;  // per block: kMacroPartialDoubles
     double *result;    // 6 doubles, device or mapped host memory
-    unsigned *done;    // count of finished blocks (0 between launches): the last block merges; nullptr: a second launch does
 };
 
 constexpr int kMacroPartialDoubles = 10;  // mass(s,c) err2(s,c) ref2(s,c) maxerr maxphi nonfinite pad
 constexpr int kMacroBlocks = 1024;
-// Blocks up to which the reduction's last block merges the partials; of more, the count and the uncached reads of
-// the partials cost more than a second launch (us per lbm_macros call, one launch / two: 512^2 FP32, 1024 blocks
-// 35.5 / 29.0; 401^2 FP64, 629 blocks 29.4 / 26.3; 128^2, 64 blocks 20 / 23).
-constexpr int kMacroFusedBlocks = 256;
 
 struct PopArgs {
     const void *src;
@@ -241,7 +236,7 @@ hipError_t launch_init(int mode, const InitArgs &a, hipStream_t st);
 // F16SR: sets *slot = level (one lane of one block; kept out of graph captures by the callers).
 hipError_t launch_set_clock(int64_t *slot, int64_t level, hipStream_t st);
 hipError_t launch_prep(int mode, const PrepArgs &a, hipStream_t st);
-hipError_t launch_macros(int mode, MacroArgs a, hipStream_t st);
+hipError_t launch_macros(int mode, const MacroArgs &a, hipStream_t st);
 hipError_t launch_macros_finalize(const MacroArgs &a, int nblocks, hipStream_t st);
 hipError_t launch_populations(int mode, const PopArgs &a, hipStream_t st);
 // D2Q9 state images between the standard layout and the one-buffer layout after a streaming step

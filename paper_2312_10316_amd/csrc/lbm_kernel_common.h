@@ -215,24 +215,18 @@ __device__ inline void block_reduce(CSum (&cs)[3], double &mx0, double &mx1, dou
     }
 }
 
-// One block: merges the partials of nblocks blocks; result[0..2] = mass, sum err^2, sum ref^2 (s + c),
-// result[3] = max err, result[4] = max |phi|, result[5] = non-finite count.  The partials are read and written
-// as agent-scope atomics, which see each other from every XCD.
-__device__ __forceinline__ double agent_load(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void agent_store(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// One block: merges the partials of nblocks blocks of an earlier launch; result[0..2] = mass, sum err^2, sum ref^2
+// (s + c), result[3] = max err, result[4] = max |phi|, result[5] = non-finite count.
 __device__ inline void macros_merge(const double *partials, int nblocks, double *result)
 {
     CSum cs[3] = {{0, 0}, {0, 0}, {0, 0}};
     double mx0 = 0, mx1 = 0, cnt = 0;
     for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
         const double *p = partials + (int64_t)b * kMacroPartialDoubles;
-        double v[9];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) v[k] = agent_load(p + k);
-        for (int k = 0; k < 3; ++k) cs[k] = csum_merge(cs[k], CSum{v[2 * k], v[2 * k + 1]});
-        mx0 = fmax(mx0, v[6]);
-        mx1 = fmax(mx1, v[7]);
-        cnt += v[8];
+        for (int k = 0; k < 3; ++k) cs[k] = csum_merge(cs[k], CSum{p[2 * k], p[2 * k + 1]});
+        mx0 = fmax(mx0, p[6]);
+        mx1 = fmax(mx1, p[7]);
+        cnt += p[8];
     }
     block_reduce(cs, mx0, mx1, cnt);
     if (threadIdx.x == 0) {
@@ -243,33 +237,22 @@ __device__ inline void macros_merge(const double *partials, int nblocks, double 
     }
 }
 
-// End of a diagnostics kernel: the block's partials, and with a.done the merge by the last block to finish (a
-// second launch is 3 us of a call on a small lattice).  The partials have left the wave (vmcnt 0) before the
-// block is counted; an agent-scope release would write back every dirty line of the XCD's L2 (a batch's 32^2 to
-// 512^2 lattices: 13.3 us per launch, 11.4 so).  The last block leaves the count at 0 for the next launch.
+// End of a diagnostics kernel: the block's partials, which a second launch merges.  (Merging in the last block to
+// finish needs the partials as agent-scope atomics, whose reads pass the L2: us per lbm_macros call so / with a
+// second launch, 64^2 19.1 / 19.4, 256^2 22.4 / 19.7, 512^2 27.7 / 24.5, 128 lattices of 32^2 to 512^2 level.)
 __device__ inline void macros_end(const MacroArgs &a, CSum (&cs)[3], double maxerr, double maxphi, double nonfinite)
 {
     block_reduce(cs, maxerr, maxphi, nonfinite);
-    __shared__ bool last;
     if (threadIdx.x == 0) {
         double *p = a.partials + (int64_t)blockIdx.x * kMacroPartialDoubles;
         for (int k = 0; k < 3; ++k) {
-            agent_store(p + 2 * k, cs[k].s);
-            agent_store(p + 2 * k + 1, cs[k].c);
+            p[2 * k] = cs[k].s;
+            p[2 * k + 1] = cs[k].c;
         }
-        agent_store(p + 6, maxerr);
-        agent_store(p + 7, maxphi);
-        agent_store(p + 8, nonfinite);
-        if (a.done) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-        }
+        p[6] = maxerr;
+        p[7] = maxphi;
+        p[8] = nonfinite;
     }
-    if (!a.done) return;
-    __syncthreads();
-    if (!last) return;
-    macros_merge(a.partials, (int)gridDim.x, a.result);
-    if (threadIdx.x == 0) __hip_atomic_store(a.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 inline int grid_for(int64_t n, int block, int cap)

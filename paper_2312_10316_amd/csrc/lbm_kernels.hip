@@ -790,10 +790,9 @@ hipError_t launch_prep(int mode, const PrepArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_macros(int mode, MacroArgs a, hipStream_t st)
+hipError_t launch_macros(int mode, const MacroArgs &a, hipStream_t st)
 {
     const int g = grid_for((int64_t)a.L.nx * a.L.ny, 256, kMacroBlocks);
-    if (g > kMacroFusedBlocks) a.done = nullptr;
     switch (mode) {
     case MODE_F64_F64: macros_kernel<MODE_F64_F64><<<g, 256, 0, st>>>(a); break;
     case MODE_F64_F32: macros_kernel<MODE_F64_F32><<<g, 256, 0, st>>>(a); break;
@@ -803,7 +802,7 @@ hipError_t launch_macros(int mode, MacroArgs a, hipStream_t st)
     default: return hipErrorInvalidValue;
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || a.done) return e;
+    if (e != hipSuccess) return e;
     return launch_macros_finalize(a, g, st);
 }
 

@@ -867,10 +867,9 @@ hipError_t launch_init3_q(int mode, const InitArgs &a, hipStream_t st)
 }
 
 template <int Q>
-hipError_t launch_macros3_q(int mode, MacroArgs a, hipStream_t st)
+hipError_t launch_macros3_q(int mode, const MacroArgs &a, hipStream_t st)
 {
     const int g = grid_for((int64_t)a.L.nx * a.L.ny * a.L.nz, 256, kMacroBlocks);
-    if (g > kMacroFusedBlocks) a.done = nullptr;
     switch (mode) {
     case MODE_F64_F64: macros3_kernel<Q, MODE_F64_F64><<<g, 256, 0, st>>>(a); break;
     case MODE_F64_F32: macros3_kernel<Q, MODE_F64_F32><<<g, 256, 0, st>>>(a); break;
@@ -879,7 +878,7 @@ hipError_t launch_macros3_q(int mode, MacroArgs a, hipStream_t st)
     default: return hipErrorInvalidValue;
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || a.done) return e;
+    if (e != hipSuccess) return e;
     return launch_macros_finalize(a, g, st);
 }
 
