@@ -156,7 +156,10 @@ int lbm_workspace_size(int32_t n_inst, const lbm_params *p, size_t *bytes);
  * lbm_free; or NULL, in which case the library allocates (and later frees) its own.
  * stream: hipStream_t for all later work, or NULL.  Synchronizes the stream once (to check the
  * F16S range: LBM_E_ARG if |g_eq - w_i phi_ref| * 2^scale_log2 would overflow FP16).
- * On success *ctx is set; on failure *ctx is NULL and nothing is owned. */
+ * The first context of a process also allocates one 4 KB page of pinned host memory, for the results of
+ * lbm_macros; it serves 64 contexts at a time (more read theirs from the device) and is kept until the process
+ * ends, as the static array of lbm_macros_static is.
+ * On success *ctx is set; on failure *ctx is NULL and nothing else is owned. */
 int lbm_init(lbm_ctx **ctx, int32_t n_inst, const lbm_params *p, const lbm_fields *f,
              void *workspace, size_t workspace_bytes, void *stream);
 
@@ -396,8 +399,8 @@ int lbm_bench_copy(void *dst, const void *src, size_t bytes, void *stream);
  * step whose state is held in that cache can reach.  Same arguments and errors. */
 int lbm_bench_copy_cached(void *dst, const void *src, size_t bytes, void *stream);
 
-/* Synchronizes the context's stream and releases everything the library allocated (never caller
- * memory).  NULL is accepted. */
+/* Synchronizes the context's stream and releases everything the library allocated for the context (never
+ * caller memory).  NULL is accepted. */
 int lbm_free(lbm_ctx *ctx);
 
 /* Message for the calling thread's most recent failed call ("" if none).  Never NULL. */
