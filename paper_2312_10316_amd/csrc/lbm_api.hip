@@ -363,6 +363,7 @@ struct Instance {
     char *alt;   // the workspace's second population buffer (buf[1] unless the instance runs in place)
     void *u, *k, *s, *bc;
     lbm_launch shape;  // the default launch shape as reported
+    Launch lc0, lc10;  // the launches (lc, lc1) that go with it
     bool shape_on;     // it is set
     bool flat_ok;      // single steps of that shape run on the gapless 3D kernel
     bool one_ok;       // that shape (two buffers) runs on one buffer in place
@@ -504,6 +505,7 @@ struct lbm_ctx {
     lbm_batch strips_batch = {};      // the default batch schedule
     bool strips_on = false;           // that schedule and every instance's default shape are set: strips run
     bool l2_streams = false;          // steps stream their stores although the state fits the caches
+    bool l2_streams0 = false;         // with the default launch shape
     lbm_batch batch = {LBM_BATCH_SERIAL, 0, 0};
     InstDesc *d_desc = nullptr;       // device tables (in the workspace)
     std::vector<InstDesc> h_desc;     // host staging of the descriptors
@@ -1292,7 +1294,12 @@ int lbm_init(lbm_ctx **out, int32_t n_inst, const lbm_params *p, const lbm_field
         in0.lc.max_waves = in0.lc1.max_waves = 0;
         in0.lc.lds_reserve = in0.lc1.lds_reserve = 0;
     }
-    for (Instance &in : c->inst) in.flat_ok = flat_default(in);
+    for (Instance &in : c->inst) {
+        in.flat_ok = flat_default(in);
+        in.lc0 = in.lc;
+        in.lc10 = in.lc1;
+    }
+    c->l2_streams0 = c->l2_streams;
     update_strips(c);
 
     // Zero everything the library owns (padding columns included) so that a state is a
@@ -1557,8 +1564,12 @@ int lbm_set_launch(lbm_ctx *c, int32_t inst, const lbm_launch *cfg)
     if (!c || inst < -1 || inst >= (int32_t)c->inst.size())
         return fail(LBM_E_STATE, "lbm_set_launch: bad context or instance %d", inst);
     if (!cfg) return fail(LBM_E_ARG, "lbm_set_launch: cfg is NULL");
+    lbm_launch given = *cfg;  // as lbm_get_launch reports it
+    given.fuse = given.fuse == 0 ? 1 : given.fuse;
+    given.xcd_rows = given.xcd_remap == 3 ? given.xcd_rows : 0;
+    const auto is_default = [&given](const Instance &in) { return std::memcmp(&given, &in.shape, sizeof given) == 0; };
     lbm_launch one = *cfg;  // the default shape of an instance that then runs on one buffer in place
-    const bool hide = c->inst[0].one_ok && std::memcmp(cfg, &c->inst[0].shape, sizeof *cfg) == 0;
+    const bool hide = c->inst[0].one_ok && is_default(c->inst[0]);
     if (hide) {
         one.stores = 2;
         cfg = &one;
@@ -1631,8 +1642,13 @@ int lbm_set_launch(lbm_ctx *c, int32_t inst, const lbm_launch *cfg)
         in.lc = lc;
         if (!two) in.lc1 = lc;  // fused: single steps keep a one-step launch of the same store kind
         else in.lc1.stores = lc.stores;
+        if (is_default(in)) {  // the default shape again: its single steps too
+            in.lc = in.lc0;
+            in.lc1 = in.lc10;
+        }
     }
-    c->l2_streams = false;  // the caller's store kind holds for the adjoint's recomputation too
+    // a caller's own store kind holds for the adjoint's recomputation too
+    c->l2_streams = c->l2_streams0 && is_default(c->inst[0]);
     c->inst[0].one_on = hide;
     update_strips(c);
     return refresh_tables(c);
