@@ -240,25 +240,24 @@ int pair_rows(int nx, int ny, int64_t &units)
     return best;
 }
 
-// Rows of a strip of T steps on an nx x ny lattice.  A strip of H rows computes T H + T (T - 1) node rows
-// (T H + 2 T (T - 1) in the flux form; each step's rows beyond the strip's are recomputed by its
+// Rows of a strip of T steps on an nx x ny lattice.  A strip of H rows computes T H + T (T - 1) node rows (each
+// step's rows beyond the strip's are recomputed by its
 // neighbours), so tall strips waste less and short ones fill the chip.  Time of a launch in units of one
 // node row at full issue rate: 12 for the launch, and per generation of resident waves (`occ` per SIMD)
 // alone[w] per node row with w waves on a SIMD, from runs at 64^2 .. 2048^2 (FP32 0.32 / 0.41 / 0.57 us, FP64
 // 0.32 / 0.57 us per node row with 1 / 2 / 3 waves), times a term for the rows that two strips read:
 // 1024^2 FP32 10 rows 169k MLUPS, 12 rows 154k, 4 rows 140k; 2048^2 38 rows 206k, 26 rows 200k, 16 rows 191k.
 // From eight generations of 16-row strips on the count no longer matters: 24 rows (with two waves per SIMD
-// FP32 8192^2 223k MLUPS, 16 rows 212k; FP64 125.6k, 123.2k), in the flux form 64 (FP32 8192^2 198k, 32
-// rows 186k; FP64 4096^2 82.8k, 24 rows 74.5k; FP16 8192^2 157k, 144k).
-int strip_rows(int mode, int nx, int ny, bool flux)
+// FP32 8192^2 223k MLUPS, 16 rows 212k; FP64 125.6k, 123.2k).
+int strip_rows(int mode, int nx, int ny)
 {
     const bool f64 = mode == MODE_F64_F64;
     const double alone[4] = {0.0, f64 ? 1.92 : 1.9, f64 ? 3.42 : 2.46, 3.4};
-    const int occ = f64 ? 2 : 3, T = flux ? kFluxStripSteps : kStripSteps;
-    const int V = strip_width(flux ? 2 * T : T, 1), extra = (flux ? 2 : 1) * T * (T - 1);
+    constexpr int occ_f64 = 2, occ_f32 = 3, T = kStripSteps, V = strip_width(T, 1), extra = T * (T - 1);
+    const int occ = f64 ? occ_f64 : occ_f32;
     const int64_t ns = (nx + V - 1) / V;
     const auto per_simd = [&](int h) { return (double)(ns * ((ny + h - 1) / h)) / 1024.0; };
-    if (per_simd(16) >= 8.0) return flux ? 64 : 24;
+    if (per_simd(16) >= 8.0) return 24;
     int best = 1;
     double least = 0.0;
     for (int h = 1; h <= 40; ++h) {
@@ -270,6 +269,32 @@ int strip_rows(int mode, int nx, int ny, bool flux)
             least = t;
         }
     }
+    return best;
+}
+
+// The same for the flux form, whose strips compute T H + 2 T (T - 1) node rows of many more instructions, so that a
+// second wave on a SIMD hides little: us of a launch = 8.5 + rows alone(w), w strips on the fullest SIMD, from 1 to
+// 64 rows at 64 x 4000 and 650^2 (650^2 with D, 5 rows of two waves / 9 rows of one, us per
+// step: FP16 11.0 / 8.8, FP32 9.5 / 7.9, FP64 with FP32 math 10.6 / 8.8).  64 rows from eight generations of 16-row
+// strips on (FP32 8192^2 198k, 32 rows 186k; FP64 4096^2 82.8k, 24 rows 74.5k; FP16 8192^2 157k, 144k).
+int flux_strip_rows(int mode, bool has_D, int nx, int ny)
+{
+    constexpr int T = kFluxStripSteps, V = strip_width(2 * T, 1);
+    const int64_t ns = (nx + V - 1) / V;
+    // alone(1), (2), (3), and each further wave; without and with D
+    static constexpr double us_row[4][2][4] = {{{0.40, 0.90, 1.43, 0.53}, {0.49, 1.08, 1.72, 0.63}},    // FP64
+                                               {{0.34, 0.555, 0.91, 0.33}, {0.415, 0.74, 1.17, 0.40}},  // FP64 storage, FP32 math
+                                               {{0.29, 0.44, 0.645, 0.24}, {0.38, 0.67, 0.96, 0.345}},  // FP32
+                                               {{0.34, 0.60, 0.97, 0.36}, {0.44, 0.80, 1.28, 0.465}}};  // FP16
+    const double *alone = us_row[mode == MODE_F64_F64 ? 0 : mode == MODE_F64_F32 ? 1 : mode == MODE_F32_F32 ? 2 : 3][has_D ? 1 : 0];
+    const auto launch = [&](int h) {
+        const int w = (int)std::ceil(1.02 * (double)(ns * ((ny + h - 1) / h)) / 1024.0);
+        return 8.5 + (T * h + 2 * T * (T - 1)) * (w <= 3 ? alone[w - 1] : alone[2] + (w - 3) * alone[3]);
+    };
+    int best = 64;
+    if (ns * ((ny + 15) / 16) < 8 * 1024)
+        for (int h = 1; h < 64; ++h)
+            if (launch(h) < launch(best)) best = h;
     return best;
 }
 
@@ -854,6 +879,11 @@ StripLaunch rest_of(StripLaunch s)
 // per node that the tiles cover, 7.3e-6 with D, a tenth more up to 2048 columns): us per step, tiles / strips,
 // 8192^2 391 / 408 (pulse; 421 / 408 on a dense field) and with D 490 / 443; 4096^2 109 / 112 and 129 / 121; 6100 x
 // 2000 72 / 79; 300 x 60000 206 / 136; 512 x 60000 220 / 222; 2000 x 20000 290 / 240.
+// The flux form with a D field, which forms the relaxation in every step, stays on single steps where strips have
+// few columns or rows to share that among: 49 to 64 columns, of which the second strip has little, by up to 130000
+// nodes (64 x 2000 FP16 5.5 / 6.4 us per step, FP32 5.2 / 5.7; 64 x 4000 level; FP64 storage with FP32 math
+// level; FP64 up to 64 columns and 66000 nodes, 64 x 1000 5.5 / 6.0, 64^2 4.7 / 5.0), and FP16 on fewer than 24 rows of which every SIMD has
+// a full-height strip already (60000 x 16 17.4 / 19.6).
 // Stores: the default launch's kind (cached within the Infinity Cache); FP32 and FP16 states of more
 // than twice that cache are stored cached too, which merges the lines that neighbouring strips share
 // (FP32 8192^2 208k streaming / 220k cached, 4096^2 206k / 216k, FP16 8192^2 218k / 223k; 2048^2 FP32, 1.3
@@ -898,7 +928,12 @@ StripLaunch strip_default(const lbm_ctx *c, size_t touched, bool batch_fuses)
     if (walls && in.mode == MODE_F64_F32) return s;
     if (f16 && !pairs && !walls && in.p.nx <= 2048 && (in.p.nx + 511) / 512 * 512 - in.p.nx <= 64 && nodes >= fuse_min_nodes(in.mode))
         return s;
-    s.rows = pairs ? prows : strip_rows(in.mode, in.p.nx, in.p.ny, flux);
+    if (flux && in.has_D) {
+        const bool f64 = in.mode == MODE_F64_F64;
+        if (in.p.nx <= 64 && (f64 ? nodes <= 66000 : in.p.nx > 48 && nodes <= 130000 && in.mode != MODE_F64_F32)) return s;
+        if (f16 && in.p.ny < 24 && in.p.nx >= 48000) return s;
+    }
+    s.rows = pairs ? prows : flux ? flux_strip_rows(in.mode, in.has_D, in.p.nx, in.p.ny) : strip_rows(in.mode, in.p.nx, in.p.ny);
     s.cols = pairs ? 2 : 1;
     s.steps = flux ? kFluxStripSteps : kStripSteps;
     if (in.mode == MODE_F32_F32 && !flux && !walls) s.lds_reserve = lds_reserve_for(nodes >= 7000000 ? 2 : 3, c->lds_per_cu);

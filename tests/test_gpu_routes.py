@@ -97,6 +97,21 @@ def test_flux_strips(mode, nx, ny, stores):
         compare(mode, nx, ny, FLUX, var, dict(kind=STRIPS, steps=4, stores=stores, cols=48), (4, 7, 70), source=var)
 
 
+@pytest.mark.parametrize("mode,nx,ny,rows", [("f16s", 650, 650, (8, 12)), ("f32", 650, 650, (8, 12)), ("f16s", 64, 4000, (8, 10)), ("f64", 650, 650, (9, 12))])
+def test_flux_strips_one_per_simd(mode, nx, ny, rows):
+    """Two short strips on a SIMD take longer than one of twice the rows (650^2 FP16 with D, us per step: 5 rows 11.0, 9
+    rows 8.8)."""
+    s = Solver([(lbm.make_params(nx, ny, 1.0, 1.0, 0.25, 0.02, mode, FLUX, phi_ref=1.0), fields(nx, ny, var=True))])
+    got = lbm.lbm_launch_route(s.ctx)
+    assert got["kind"] == STRIPS and rows[0] <= got["rows"] <= rows[1], got
+    assert -(-nx // 48) * -(-ny // got["rows"]) <= 1024
+
+
+@pytest.mark.parametrize("mode,nx,ny", [("f16s", 64, 2000), ("f32", 64, 2000), ("f64", 64, 1000), ("f64", 40, 300), ("f16s", 60000, 16)])
+def test_flux_form_with_d_on_single_steps(mode, nx, ny):
+    compare(mode, nx, ny, FLUX, True, dict(kind=lbm.LBM_ROUTE_TILES, steps=1), (4, 7))
+
+
 @pytest.mark.parametrize("mode", ["f64", "f32", "f16s"])
 @pytest.mark.parametrize("nx,ny", [(57, 12017), (1500, 1001), (2500, 1407)])
 def test_strips_between_walls(mode, nx, ny):
