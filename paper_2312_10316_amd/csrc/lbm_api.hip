@@ -390,7 +390,7 @@ struct Instance {
     lbm_launch shape;  // the default launch shape as reported
     Launch lc0, lc10;  // the launches (lc, lc1) that go with it
     bool shape_on;     // it is set
-    bool flat_ok;      // single steps of that shape run on the gapless 3D kernel
+    int32_t flat;      // Launch::flat of that shape's single steps
     bool one_ok;       // that shape (two buffers) runs on one buffer in place
     bool one_on;       // it is set, and does
     bool has_D;
@@ -702,17 +702,8 @@ void update_strips(lbm_ctx *c)
         const bool same = std::memcmp(&now, &in.shape, sizeof now) == 0;
         in.shape_on = same;
         c->strips_on = c->strips_on && same;
-        in.lc.flat = in.lc1.flat = same && in.flat_ok ? 1 : 0;
+        in.lc.flat = in.lc1.flat = same ? in.flat : 0;
     }
-}
-
-// Lattices whose single steps run on the gapless 3D kernel in their default launch shape: with row tiles more
-// than a quarter of the lanes would be idle, cached stores, at least 32 columns (a wave then spans at most
-// three rows), and 32-bit offsets.  (100 to 200 columns measured level or, FP16 D3Q27, 12 % slower.)
-bool flat_default(const Instance &in)
-{
-    return is3d(in) && in.lc.stores == 1 && in.p.nx >= 32 && (in.p.nx + 63) / 64 * 64 > 1.34 * in.p.nx &&
-           pops_bytes(in.p) <= UINT32_MAX && vel_bytes(in.p) <= UINT32_MAX;
 }
 
 // Bytes of the cache lines (128 B) that a 3D instance's steps touch with `bufs` population buffers: rows of a
@@ -721,6 +712,17 @@ size_t lines_touched(const Instance &in, int bufs)
 {
     const auto row = [&](size_t elem) { return align_up((size_t)in.L.nx * elem, 128); };
     return (size_t)rows_of(in.L) * (bufs * in.L.q * row(store_bytes(in.mode)) + (dim_of(in.L) + (in.has_D ? 1 : 0)) * row(math_bytes(in.mode)));
+}
+
+// Lattices whose single steps run on the gapless 3D kernel in their default launch shape: with row tiles more
+// than a quarter of the lanes would be idle, cached stores, at least 32 columns (a wave then spans at most
+// three rows), and 32-bit offsets.  (100 to 200 columns measured level or, FP16 D3Q27, 12 % slower.)
+int32_t flat_default(const Instance &in)
+{
+    if (!is3d(in) || in.lc.stores != 1 || in.p.nx < 32 || (in.p.nx + 63) / 64 * 64 <= 1.34 * in.p.nx ||
+        pops_bytes(in.p) > UINT32_MAX || vel_bytes(in.p) > UINT32_MAX)
+        return 0;
+    return lines_touched(in, 2) <= kInfinityCacheBytes / 4 * 3 ? 2 : 1;
 }
 
 // Rebuilds the descriptors and (for a batched policy) the work list, and uploads them.  The host
@@ -1330,7 +1332,7 @@ int lbm_init(lbm_ctx **out, int32_t n_inst, const lbm_params *p, const lbm_field
         in0.lc.lds_reserve = in0.lc1.lds_reserve = 0;
     }
     for (Instance &in : c->inst) {
-        in.flat_ok = flat_default(in);
+        in.flat = flat_default(in);
         in.lc0 = in.lc;
         in.lc10 = in.lc1;
     }

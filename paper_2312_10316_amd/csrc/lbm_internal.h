@@ -58,7 +58,8 @@ struct Launch {
     int32_t stores;       // 0: non-temporal stores of the new state; 1: cached; 2: one buffer in place, cached
     int32_t fuse;         // time steps per launch: 1 (0 reads as 1), or 2 (step2_kernel, lbm_fused.hip)
     int32_t fuse_width;   // fused launches: output columns per tile (128, 256 or 512); rows = tile height
-    int32_t flat;         // 3D one-step launches: nodes dealt to the lanes without gaps (step3_flat_kernel)
+    int32_t flat;         // 3D one-step launches: 1 nodes dealt to the lanes without gaps (step3_flat_kernel); 2 the same,
+                          // a state whose cache lines fit three quarters of the Infinity Cache
 };
 
 // Everything a step kernel needs about one instance.  Single-instance launches pass it by value;

@@ -341,9 +341,14 @@ __global__ __launch_bounds__(256) void step3_kernel(const StepArgs sa)
 // state must be smaller than 4 GiB.  Cached stores (a wave's segments start inside cache lines, which streaming
 // stores write in parts: D3Q19 FP16 250^3 274 -> 366 us).  The same arithmetic, bitwise.  Per step, row tiles /
 // gapless: D3Q19 FP32 45 x 200 x 100 33.2 / 22.6 us, FP16 45 x 50 x 60 6.9 / 6.3, D3Q27 FP32 70 x 60 x 40
-// 13.0 / 9.8, FP64 40 x 50 x 60 13.6 / 11.0.
-template <int Q, int MODE, int AUX, bool HAS_K, bool HAS_S>
-__global__ __launch_bounds__(256) void step3_flat_kernel(const StepArgs sa)
+// 13.0 / 9.8, FP64 40 x 50 x 60 13.6 / 11.0.  W: waves per
+// SIMD that the compiler may take registers for (0: its own choice).  D3Q19 FP64 in the local form without a D field
+// it had given 92 registers, for five waves, and waited for the loads in parts; with four waves and 112 a state
+// well within the Infinity Cache is the faster (80^3 row tiles 27.7 us, five waves 29.3, four 26.3; 40^3 7.3, 6.1,
+// 5.2), one of more than three quarters of it in cache lines not (82^3 44.2, 38.9, 41.0; 85^3 49.1, 40.8, 44.5).
+template <int Q, int MODE, int AUX, bool HAS_K, bool HAS_S, int W = 0>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W ? W : 1, W ? W : 8)))
+void step3_flat_kernel(const StepArgs sa)
 {
     using St = typename ModeTraits<MODE>::St;
     using M = typename ModeTraits<MODE>::M;
@@ -781,8 +786,17 @@ hipError_t launch_step3_flat(const StepArgs &a, hipStream_t st)
     const bool hk = a.d.has_k, hs = a.d.has_s;
     if (hk && hs) step3_flat_kernel<Q, MODE, AUX, true, true><<<nb, 256, lds, st>>>(a);
     else if (hk) step3_flat_kernel<Q, MODE, AUX, true, false><<<nb, 256, lds, st>>>(a);
-    else if (hs) step3_flat_kernel<Q, MODE, AUX, false, true><<<nb, 256, lds, st>>>(a);
-    else step3_flat_kernel<Q, MODE, AUX, false, false><<<nb, 256, lds, st>>>(a);
+    else {
+        if constexpr (Q == 19 && MODE == MODE_F64_F64 && AUX == 0) {
+            if (a.d.lc.flat == 2) {
+                if (hs) step3_flat_kernel<Q, MODE, AUX, false, true, 4><<<nb, 256, lds, st>>>(a);
+                else step3_flat_kernel<Q, MODE, AUX, false, false, 4><<<nb, 256, lds, st>>>(a);
+                return hipGetLastError();
+            }
+        }
+        if (hs) step3_flat_kernel<Q, MODE, AUX, false, true><<<nb, 256, lds, st>>>(a);
+        else step3_flat_kernel<Q, MODE, AUX, false, false><<<nb, 256, lds, st>>>(a);
+    }
     return hipGetLastError();
 }
 

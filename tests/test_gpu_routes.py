@@ -159,6 +159,11 @@ def test_gapless_3d(q, mode, nx, ny, nz):
         compare(mode, nx, ny, aux, var, dict(kind=GAPLESS, steps=1, stores=1), (1, 2, 67), nz=nz, q=q, source=var)
 
 
+def test_gapless_3d_beyond_three_quarters_of_the_cache():
+    """D3Q19 FP64 without a D field: the small sizes above take four waves per SIMD, this one the compiler's choice."""
+    compare("f64", 82, 82, LOCAL, False, dict(kind=GAPLESS, steps=1, stores=1), (1, 2, 67), nz=82, q=19, source=True)
+
+
 @pytest.mark.parametrize("q,mode,nx,ny,nz,stores", [(19, "f32", 100, 100, 80, 1), (27, "f32", 100, 100, 80, 1),
                                                     (19, "f32", 240, 224, 64, 0), (19, "f64", 100, 100, 78, 1),
                                                     (19, "f64", 100, 100, 90, 0), (27, "f64", 100, 100, 80, 0)])
