@@ -1871,8 +1871,15 @@ int lbm_adjoint_segment(lbm_ctx *c, int32_t inst, void *states, int32_t nsteps, 
     // 2500^2 2236 / 2258 / 2221; FP64 384^2 122 / 96 / 106, 1000^2 689 / 625 / 609; and the reverse sweep on 12 / on
     // 16: FP32 384^2 63 / 69 (single 76), 1000^2 289 / 283; FP64 storage with FP32 math 2048^2 1718 / 1755 (2098).
     const int waves = (int64_t)in.p.nx * in.p.ny < 300000 ? 12 : 16, adj_waves = in.mode == MODE_F64_F32 ? 12 : waves;
+    // Where a patch hangs over an FP64 lattice, single steps are the faster: of three rows of its ten on 1.2e6 nodes
+    // (400000 x 3, segment of 9: 804 us, on patches 874; 100000 x 3 208 / 195), and for the reverse sweep of a segment of
+    // four on up to eight columns, whose one launch leaves lam in the other array, to be copied with its padding
+    // (3 x 20000 162 / 181, 8 x 20000 162 / 183; 8 x 8000 85 / 78).
+    const int64_t nodes = (int64_t)in.p.nx * in.p.ny;
+    const bool f64 = in.mode == MODE_F64_F64, few_rows = f64 && in.p.ny < 4 && nodes >= 1000000;
+    const bool one_launch = f64 && nsteps == kAdjointPatchSteps && in.p.nx <= 8 && in.p.ny >= 16000;
     int32_t j = 0;
-    for (; in.shape_on && j + kPatchImages < nsteps; j += kPatchImages) {
+    for (; in.shape_on && !few_rows && j + kPatchImages < nsteps; j += kPatchImages) {
         a.d.buf[0] = img + (size_t)j * sb;
         a.d.buf[1] = img + (size_t)(j + 1) * sb;
         hipError_t e = launch_patch_images(in.mode, in.p.aux, a, waves, (int64_t)sb, c->stream);
@@ -1888,7 +1895,7 @@ int lbm_adjoint_segment(lbm_ctx *c, int32_t inst, void *states, int32_t nsteps, 
     AdjArgs g = adj_args(in, dLdD);
     void *cur = lam, *nxt = lam_tmp;
     j = nsteps - 1;
-    for (; j + 1 >= kAdjointPatchSteps; j -= kAdjointPatchSteps) {
+    for (; !few_rows && !one_launch && j + 1 >= kAdjointPatchSteps; j -= kAdjointPatchSteps) {
         g.state = img + (size_t)j * sb;
         g.lam_in = cur;
         g.lam_out = nxt;

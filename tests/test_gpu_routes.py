@@ -188,3 +188,29 @@ def test_batched_strips(mode):
         two.step(n, S=src)
         for k in range(3):
             assert torch.equal(one.state_save(k), two.state_save(k))
+
+
+@pytest.mark.parametrize("nx,ny,steps", [(8, 16000, 4), (3, 16001, 9), (333334, 3, 9)])
+def test_adjoint_segments_that_hang_over_patches(nx, ny, steps):
+    """FP64 segments that a rule keeps off the patches (all, or one of four steps) against lbm_adjoint_step."""
+    f = fields(nx, ny, var=True)
+    p = lbm.make_params(nx, ny, 1.0, 1.0, 0.25, 0.02, "f64")
+    one, two = Solver([(p, f)]), Solver([(p, f)])
+    one.set_launch(1, 1, tile_width=256, stores=0)
+    sb, nb = lbm.lbm_state_bytes(two.ctx), lbm.lbm_adjoint_bytes(two.ctx)
+    images = torch.zeros(steps * sb, dtype=torch.uint8, device="cuda")
+    images[:sb].copy_(two.state_save())
+    lam, tmp, ref, out = (torch.zeros(nb, dtype=torch.uint8, device="cuda") for _ in range(4))
+    grad, want = (torch.zeros((ny, nx), dtype=torch.float64, device="cuda") for _ in range(2))
+    for ctx, t in ((two.ctx, lam), (one.ctx, ref)):
+        lbm.lbm_adjoint_seed(ctx, 0, f["phi0"], t)
+    lbm.lbm_adjoint_segment(two.ctx, 0, images, steps, lam, tmp, grad)
+    states = [one.state_save()]
+    for _ in range(steps - 1):
+        one.step(1)
+        states.append(one.state_save())
+    for j in reversed(range(steps)):
+        lbm.lbm_adjoint_step(one.ctx, 0, states[j], ref, out, want)
+        ref, out = out, ref
+    nodes = lambda t: t.view(torch.float64).view(ny, 9, -1)[:, :, :nx]
+    assert torch.equal(nodes(lam), nodes(ref)) and torch.equal(grad, want)
