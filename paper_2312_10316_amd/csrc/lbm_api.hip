@@ -716,13 +716,17 @@ size_t lines_touched(const Instance &in, int bufs)
 
 // Lattices whose single steps run on the gapless 3D kernel in their default launch shape: with row tiles more
 // than a quarter of the lanes would be idle, cached stores, at least 32 columns (a wave then spans at most
-// three rows), and 32-bit offsets.  (100 to 200 columns measured level or, FP16 D3Q27, 12 % slower.)
+// three rows), and 32-bit offsets.  (100 to 200 columns measured level or, FP16 D3Q27, 12 % slower.)  Not D3Q19 FP64
+// without aux term whose cache lines exceed 300 MiB (36 x 36 x 600 57.5 us on row tiles, 60.1 gapless, with D 62.5 / 66.1;
+// 33 x 150 x 150 with D 72.4 / 78.0; 277 MiB, 40 x 100 x 180 with D 50.1 / 46.1; the local form 73.2 / 64.5).
 int32_t flat_default(const Instance &in)
 {
     if (!is3d(in) || in.lc.stores != 1 || in.p.nx < 32 || (in.p.nx + 63) / 64 * 64 <= 1.34 * in.p.nx ||
         pops_bytes(in.p) > UINT32_MAX || vel_bytes(in.p) > UINT32_MAX)
         return 0;
-    return lines_touched(in, 2) <= kInfinityCacheBytes / 4 * 3 ? 2 : 1;
+    const size_t lines = lines_touched(in, 2);
+    if (in.L.q == 19 && in.mode == MODE_F64_F64 && in.p.aux == LBM_AUX_NONE && lines > ((size_t)300 << 20)) return 0;
+    return lines <= kInfinityCacheBytes / 4 * 3 ? 2 : 1;
 }
 
 // Rebuilds the descriptors and (for a batched policy) the work list, and uploads them.  The host

@@ -159,6 +159,11 @@ def test_gapless_3d(q, mode, nx, ny, nz):
         compare(mode, nx, ny, aux, var, dict(kind=GAPLESS, steps=1, stores=1), (1, 2, 67), nz=nz, q=q, source=var)
 
 
+@pytest.mark.parametrize("aux,kind", [(NONE, lbm.LBM_ROUTE_TILES), (LOCAL, GAPLESS)])
+def test_narrow_3d_lattices_beyond_the_cache(aux, kind):
+    compare("f64", 36, 36, aux, True, dict(kind=kind, steps=1, stores=1), (1, 2, 67), nz=600, q=19)
+
+
 def test_gapless_3d_beyond_three_quarters_of_the_cache():
     """D3Q19 FP64 without a D field: the small sizes above take four waves per SIMD, this one the compiler's choice."""
     compare("f64", 82, 82, LOCAL, False, dict(kind=GAPLESS, steps=1, stores=1), (1, 2, 67), nz=82, q=19, source=True)
