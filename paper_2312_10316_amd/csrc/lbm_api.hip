@@ -284,7 +284,7 @@ int flux_strip_rows(int mode, bool has_D, int nx, int ny)
     // alone(1), (2), (3), and each further wave; without and with D
     static constexpr double us_row[4][2][4] = {{{0.40, 0.90, 1.43, 0.53}, {0.49, 1.08, 1.72, 0.63}},    // FP64
                                                {{0.34, 0.555, 0.91, 0.33}, {0.415, 0.74, 1.17, 0.40}},  // FP64 storage, FP32 math
-                                               {{0.29, 0.44, 0.645, 0.24}, {0.38, 0.67, 0.96, 0.345}},  // FP32
+                                               {{0.29, 0.46, 0.645, 0.24}, {0.38, 0.67, 0.96, 0.345}},  // FP32
                                                {{0.34, 0.60, 0.97, 0.36}, {0.44, 0.80, 1.28, 0.465}}};  // FP16
     const double *alone = us_row[mode == MODE_F64_F64 ? 0 : mode == MODE_F64_F32 ? 1 : mode == MODE_F32_F32 ? 2 : 3][has_D ? 1 : 0];
     const auto launch = [&](int h) {
