@@ -54,9 +54,9 @@ def roofline_bound(stores: int) -> str:
 
 def kernel_hash() -> str:
     h = hashlib.sha256()
-    for name in ("lbm_kernels.hip", "lbm_fused.hip", "lbm_strips.h", "lbm_patches.h", "lbm_kernel_common.h", "lbm_device.h", "lbm_internal.h",
-                 "lbm_api.hip"):
-        with open(os.path.join(ROOT, "paper_2312_10316_amd", "csrc", name), "rb") as fh:
+    csrc = os.path.join(ROOT, "paper_2312_10316_amd", "csrc")
+    for name in sorted(f for f in os.listdir(csrc) if f.endswith((".hip", ".h"))):
+        with open(os.path.join(csrc, name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
