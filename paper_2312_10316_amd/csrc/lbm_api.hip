@@ -872,11 +872,12 @@ StripLaunch rest_of(StripLaunch s)
 
 // The strip launch of a context in its default launch shape, or rows 0.  `touched`: bytes its steps touch.
 // One D2Q9 TRT-R instance in two buffers, periodic or between walls: patches while it is small, else strips if
-// it has at least 16 rows (a shorter lattice would recompute more than it saves); or a uniform batch of such (periodic, FP64 or FP32 storage).
-// Measured in MLUPS, without strips / with: local aux term FP32 2048^2 131k / 206k, 8192^2 140k / 223k,
-// FP64 8192^2 69k / 126k; flux form FP32 2048^2 92k / 164k, 512^2 32k / 47k, FP64 4096^2
-// 57k / 83k; walls FP32 1000 x 500 63k / 104k (patches 118k); 128 instances of 32^2 .. 512^2 FP32
-// 105k / 178k.
+// it has at least 16 rows (a shorter lattice would recompute more than it saves); or a uniform batch of such
+// (periodic, FP64 or FP32 storage; FP16 batches have no strip kernel, nor has FP64 storage with FP32 math between
+// walls: neither was built).  In MLUPS, without strips / with: local aux term FP32 2048^2 131k / 200k, 8192^2 140k /
+// 218k, FP64 8192^2 69k / 125k; flux form FP32 2048^2 99k / 153k, 512^2 32k / 47k, FP64 2048^2 55k / 80k; walls FP32
+// 1000 x 500 63k / 104k (patches 118k); 128 instances of 32^2 .. 512^2 FP32 105k / 178k.  (The figures below compare
+// variants of one sweep with each other; its rates are up to 7 % above those of long runs.)
 // Columns per lane: two for FP16 from 12e6 nodes on (even nx, local or no aux term; 8192^2 with D 180k / 219k, one
 // column 196k; 4096^2 166k / 194k, one column 171k).  FP16 states of narrow lattices that
 // fill 512-column tiles stay on two-step tiles (2048^2 203k, strips 190k; flux form 132k, 124k), as do those
@@ -888,8 +889,8 @@ StripLaunch rest_of(StripLaunch s)
 // The flux form with a D field, which forms the relaxation in every step, stays on single steps where strips have
 // few columns or rows to share that among: 49 to 64 columns, of which the second strip has little, by up to 130000
 // nodes (64 x 2000 FP16 5.5 / 6.4 us per step, FP32 5.2 / 5.7; 64 x 4000 level; FP64 storage with FP32 math
-// level; FP64 up to 64 columns and 66000 nodes, 64 x 1000 5.5 / 6.0, 64^2 4.7 / 5.0), and FP16 on fewer than 24 rows of which every SIMD has
-// a full-height strip already (60000 x 16 17.4 / 19.6).
+// level; FP64 up to 64 columns and 66000 nodes, 64 x 1000 5.5 / 6.0, 64^2 4.7 / 5.0), and FP16 on fewer than 24 rows
+// of which every SIMD has a full-height strip already (60000 x 16 17.4 / 19.6).
 // Stores: the default launch's kind (cached within the Infinity Cache); FP32 and FP16 states of more
 // than twice that cache are stored cached too, which merges the lines that neighbouring strips share
 // (FP32 8192^2 208k streaming / 220k cached, 4096^2 206k / 216k, FP16 8192^2 218k / 223k; 2048^2 FP32, 1.3

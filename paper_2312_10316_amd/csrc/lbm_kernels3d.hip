@@ -451,8 +451,8 @@ __host__ __device__ constexpr int yslots()
 // step3_kernel, so two steps are bitwise two launches of it.
 //
 // What bounds it: the one-step kernel is bound by memory (256^3 FP32 6.1 TB/s); this one moves half the bytes
-// and issues vector instructions 53 % of the time (D3Q19 FP32; 640 per two node updates), the rest being
-// the plane's barrier with one block per CU.  Times per step, one / two steps per launch: D3Q19 256^3 FP32
+// and issues vector instructions 51 % of the time (D3Q19 FP32; 394 per node and step, recomputed rows and lanes
+// included; FP64 33 %), the rest being the plane's barrier with one block per CU.  Times per step, one / two steps per launch: D3Q19 256^3 FP32
 // 453 / 365 us, FP64 955 / 703, D3Q27 FP32 638 / 550, FP64 1323 / 952; 100 x 100 x 80 D3Q19 FP32 25.9 / 20.1,
 // FP64 60.5 / 38.6, D3Q27 FP32 36.5 / 27.2, FP64 73.2 / 53.2.  FP16 storage is not built: its codec makes the
 // recomputed rows and lanes cost more than the bytes saved (D3Q19 256^3 259 / 291 us), nor is FP64 storage

@@ -19,18 +19,22 @@
 // FP16 storage on large lattices gives each lane two adjacent columns (strips of 120 columns: fewer
 // lanes lost at the ends, half the lane shifts, one 4-byte access where 2-byte ones were).
 //
-// What bounds it: VALU issue for FP32 (2048^2: 97 vector instructions per node row and step, 133 per node and
-// step with the recomputed rows and lanes, busy on 0.68 of the launch's cycles with two waves per SIMD), memory
-// and the latency of two waves per SIMD for FP64 (188 VGPRs; VALU on 0.45 of the cycles, 4.9 TB/s).  The rows before the
+// What bounds it: VALU issue for FP32 (2048^2: 133 vector instructions per node and step, the recomputed rows and
+// lanes included, busy on 0.67 of the launch's cycles; the flux form 232 and 0.90) and FP16 (two columns per lane,
+// 8192^2: 157 and all cycles), memory and the latency of two waves per SIMD for FP64 (188 VGPRs; VALU on 0.45 of the
+// cycles, 4.6 TB/s).  The rows before the
 // first output row run in a loop of their own with the steps that have no row yet skipped by uniform
 // branches; as straight code they had cost 40 VGPRs (FP32 140 -> 100).
-// Against two steps per launch through an LDS ring (lbm_fused.hip): FP32 2048^2 131k -> 206k MLUPS, 8192^2
-// 140k -> 223k, FP64 2048^2 64k -> 118k, 8192^2 69k -> 126k; flux form FP32 2048^2 92k -> 164k, 8192^2 114k ->
-// 198k, FP64 4096^2 57k -> 83k (T = 2, 56 columns: 63k); FP16 (VALU issue both ways) 8192^2 with D 180k ->
-// 210k, with stochastic rounding 141k -> 150k.  Lattices up to about 1200^2 run on patches (lbm_patches.h).  Why
-// T = 4: 56 columns start every strip on a 32-byte boundary; three steps need 58 (or waste two lanes) and
-// measured 135k at 2048^2 FP32, because the stores of neighbouring strips then share 32-byte sectors; with six
-// the carried values no longer fit the registers of FP64.
+// Against two steps per launch through an LDS ring (lbm_fused.hip), in MLUPS of long runs of the rotating pulse (one
+// card and day differs from another by up to 10 %, a dense field of FP16 codes from the pulse by 7 %): FP32 2048^2
+// 131k -> 200k, 8192^2 140k -> 218k, FP64 2048^2 64k -> 116k, 8192^2 69k -> 125k; flux form FP32 2048^2 99k -> 153k,
+// 8192^2 114k -> 194k, FP64 2048^2 55k -> 80k (T = 2, 56 columns, 4096^2: 63k, 83k with four); FP16 (VALU issue both
+// ways) 8192^2 204k -> 248k, with D 180k -> 219k and, with stochastic rounding, 141k -> 152k (without D tiles are the
+// faster).  Lattices up to about 1200^2 run on patches (lbm_patches.h).
+// Why T = 4: 56 columns start every strip of FP32 and FP64 on a 32-byte boundary; three steps need 58 (or waste two
+// lanes) and measured 135k at 2048^2 FP32, because the stores of neighbouring strips then share 32-byte sectors; with
+// six the carried values no longer fit the registers of FP64.  FP16 strips share sectors all the same (56 columns are
+// 112 bytes, 120 are 240): they are bound by issue, and whole sectors (48 or 112 columns) would cost lanes.
 #pragma once
 
 #include <type_traits>
